@@ -73,10 +73,10 @@ def listed():
         dict(name="train_fp32_c4_1024", kind="train", prec="fp32", batch=1024, n=65573,
              **net("c2")),
         # effective sample size of the benchmark's production record
-        dict(name="ess_c2_4000x4096", kind="ess", T=4000, chains=4096, d=6, rho=0.47),
+        dict(name="ess_c2_4000x4096", kind="ess", T=4000, chains=4096, d=6, rho=0.47, spread=0.0),
         # R - 1, credible limits and the sliced Wasserstein distance of a 27-parameter record
         dict(name="metrics_c5_256x4096", kind="metrics", T=256, chains=4096, d=27, rho=0.3,
-             tail=8),
+             spread=0.05, tail=8),
     ]
 
 
@@ -88,7 +88,7 @@ def _draw_net(rng):
     if rng.random() < 0.5:
         return net(rng.choice(sorted(NETS)))
     d = rng.randint(1, 32)
-    return dict(d=d, width=128 * rng.choice([1, 1, 2, 3, 4, 4, 5, 6, 8]),
+    return dict(d=d, width=rng.choice([128, 128, 256, 512, 512, 1024]),
                 n_hidden=rng.randint(1, 5), twist=d >= 4 and rng.random() < 0.25)
 
 
@@ -105,6 +105,8 @@ def draw(rng):
     if kind in ("burnin", "vjp", "train") and prec == "fp64":
         prec = "fp32"
     c = dict(kind=kind, prec=prec, **_draw_net(rng))
+    if prec == "fp64":
+        c["width"] = min(c["width"], 512)  # the widest layers an FP64 tile holds
     budget = 0.004  # seconds of emulator work at the RATE of the precision
     per = _eval_flops(c, True) / RATE[prec]
     if kind == "eval":
@@ -140,13 +142,17 @@ def draw(rng):
         c["n"] = c["batch"] * rng.randint(2, 24) + rng.randint(0, 15)
     elif kind == "ess":
         chains, T = _log_int(rng, 1, 16384), _log_int(rng, 4, 4000)
+        # chain means that differ (spread) keep the autocorrelations above zero, so every lag
+        # of the window enters, as in a record shorter than its autocorrelation
         c = dict(kind=kind, d=c["d"], chains=chains, T=T,
-                 rho=rng.choice([-0.3, 0.0, 0.47, 0.8, 0.95]))
-        c["T"] = max(4, min(T, 6 * 4096 * 4000 // (6 * c["d"] * chains)))
+                 rho=rng.choice([-0.3, 0.0, 0.47, 0.8, 0.95]),
+                 spread=rng.choice([0.0, 0.0, 0.0, 0.05]))
+        c["T"] = max(4, min(T, 6 * 4096 * 4000 // (6 * c["d"] * chains),
+                            600 if c["spread"] else 4000))
     else:
         chains = _log_int(rng, 16, 4096)
         c = dict(kind=kind, d=c["d"], chains=chains, rho=rng.choice([0.0, 0.3, 0.8]),
-                 tail=rng.randint(1, 8))
+                 spread=rng.choice([0.0, 0.05]), tail=rng.randint(1, 8))
         c["T"] = max(c["tail"], 2, min(_log_int(rng, 8, 1000),
                                        27 * 4096 * 256 // (4 * c["d"] * chains)))
     return c
@@ -268,8 +274,8 @@ def _record(c, seed, T, shift=0.0):
     e = torch.randn(T, d, n, generator=g, device="cuda")
     for t in range(1, T):
         e[t].mul_(math.sqrt(1.0 - rho * rho)).add_(e[t - 1], alpha=rho)
-    # chains that are not quite at the same mean, as after a finite burn-in
-    e += 0.05 * torch.randn(1, d, n, generator=g, device="cuda")
+    if c["spread"]:  # chains that are not quite at the same mean, as after a short burn-in
+        e += c["spread"] * torch.randn(1, d, n, generator=g, device="cuda")
     for t0 in range(0, T, 256):
         e[t0:t0 + 256] = torch.matmul(mix, e[t0:t0 + 256]) + shift
     return e, mix
