@@ -172,7 +172,6 @@ struct best_ctx {
   float *vj_h = nullptr, *vj_dl = nullptr, *vj_th = nullptr, *vj_up = nullptr;
   int64_t vj_cap = 0;
   int64_t* vj_offs = nullptr;
-  std::vector<int64_t> vj_woffs;
   NutsState nu{};
   std::vector<double> lower, upper;
   double mlp_coef = 0, offset = 0;
@@ -634,18 +633,14 @@ int best_logL_grad(best_ctx* h, const double* x, int64_t n, double* logL, double
   return BEST_OK;
 }
 
-// Offsets into the flat parameter vector: [W1, b1, b2 .. b_nh, w_out, b_out] (nh + 3) and
-// the W_l blocks (l >= 2).
-static void param_offsets(int64_t d, int64_t H, int nh, std::vector<int64_t>& offs,
-                          std::vector<int64_t>& w_offs) {
+// Offsets into the flat parameter vector: [W1, b1, b2 .. b_nh, w_out, b_out] (nh + 3).
+static void param_offsets(int64_t d, int64_t H, int nh, std::vector<int64_t>& offs) {
   const int64_t base = H * d + H, blk = H * H + H;
   offs.assign(1, 0);
   offs.push_back(H * d);
   for (int l = 2; l <= nh; ++l) offs.push_back(base + (l - 2) * blk + H * H);
   offs.push_back(base + (nh - 1) * blk);
   offs.push_back(base + (nh - 1) * blk + H);
-  w_offs.clear();
-  for (int l = 2; l <= nh; ++l) w_offs.push_back(base + (l - 2) * blk);
 }
 
 int best_logL_param_grad(best_ctx* h, const double* x, int64_t n, const double* upstream,
@@ -675,7 +670,7 @@ int best_logL_param_grad(best_ctx* h, const double* x, int64_t n, const double* 
   }
   if (!h->vj_offs) {
     std::vector<int64_t> offs;
-    param_offsets(h->d, h->H, h->nh, offs, h->vj_woffs);
+    param_offsets(h->d, h->H, h->nh, offs);
     HIPCHK(h, h->mem.upload(&h->vj_offs, offs.data(), offs.size(), h->stream));
   }
   VjpArgs a{};
@@ -699,7 +694,7 @@ int best_logL_param_grad(best_ctx* h, const double* x, int64_t n, const double* 
   const int grid = (int)std::min<int64_t>(a.n_tiles, h->grid_cap);
   HIPCHK(h, launch_vjp(h->prec, h->MT, a, grid, h->lds.total, h->stream));
   HIPCHK(h, launch_dw(h->vj_dl, h->vj_h, h->vj_th, h->vj_up, ldb, h->d, h->H, h->nh,
-                      grad_params, h->vj_offs, h->vj_woffs.data(), h->stream));
+                      grad_params, h->vj_offs, h->stream));
   return BEST_OK;
 }
 
@@ -1484,7 +1479,6 @@ struct best_trainer {
   int64_t ls_cap = 0;
   int32_t* ident = nullptr;
   int64_t* offs = nullptr;
-  std::vector<int64_t> w_offs;
 };
 
 static int tfail(best_trainer* t, int code, const std::string& msg) {
@@ -1542,7 +1536,7 @@ static int trainer_grad(best_trainer* t, const float* t_in, const float* y, cons
   const int grid = (int)std::min<int64_t>(a.n_tiles, t->grid_cap);
   THIPCHK(t, launch_train_tile(t->prec, t->MT, a, grid, t->lds.total, t->stream));
   THIPCHK(t, launch_dw(t->ex_dl, t->ex_h, t->ex_th, t->ex_up, B, t->d, t->H, t->nh, t->g,
-                       t->offs, t->w_offs.data(), t->stream));
+                       t->offs, t->stream));
   THIPCHK(t, launch_sum(t->loss_part, (int)a.n_tiles, 1.0 / (double)B, loss_out_dev, t->stream));
   return BEST_OK;
 }
@@ -1605,9 +1599,9 @@ int best_trainer_create(best_trainer** out, int32_t d, int32_t width, int32_t n_
   t->hsave_stride = (int64_t)n_hidden * width * 16 * t->MT;
   if (t->mem.alloc((char**)&t->hsave, (size_t)t->grid_cap * t->hsave_stride * 4) != hipSuccess)
     return bail(tfail(t, BEST_ENOMEM, "activation scratch"));
-  // gradient offsets: [W1, b1, b2..b_nh, w_out, b_out] and W_l (l >= 2)
+  // gradient offsets: [W1, b1, b2..b_nh, w_out, b_out]
   std::vector<int64_t> offs;
-  param_offsets(d, width, n_hidden, offs, t->w_offs);
+  param_offsets(d, width, n_hidden, offs);
   if (t->mem.upload(&t->offs, offs.data(), offs.size(), t->stream) != hipSuccess)
     return bail(tfail(t, BEST_ENOMEM, "offsets"));
   if (hipError_t e = launch_pack(precision, t->p, d, width, n_hidden, t->wf, t->wb, t->w1f,

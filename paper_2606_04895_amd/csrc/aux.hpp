@@ -56,7 +56,7 @@ hipError_t launch_adam(double* p, double* m, double* v, const double* g, int64_t
                        double b1, double b2, double eps, double c1, double c2, hipStream_t s);
 hipError_t launch_dw(const float* dl, const float* h, const float* th, const float* up,
                      int64_t B, int d, int H, int nh, double* grad, const int64_t* offs,
-                     const int64_t* w_offs_host, hipStream_t s);
+                     hipStream_t s);
 hipError_t launch_sum(const double* part, int n, double scale, double* out, hipStream_t s);
 hipError_t launch_standardise(const double* y, int64_t n, float* out, double* scratch,
                               double* stats_host, hipStream_t s);
