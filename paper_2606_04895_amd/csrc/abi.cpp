@@ -18,8 +18,7 @@ namespace best {
 #define BEST_DECL_PREC(suf)                                                                  \
   hipError_t launch_step_##suf(int, const KArgs&, int, size_t, hipStream_t);                 \
   hipError_t launch_eval_##suf(int, const KArgs&, int, size_t, hipStream_t);                 \
-  hipError_t launch_train_tile_##suf(int, const TrainArgs&, int, size_t, hipStream_t);       \
-  hipError_t launch_vjp_##suf(int, const VjpArgs&, int, size_t, hipStream_t);                \
+  hipError_t launch_fit_##suf(const FitArgs&, hipStream_t);                                  \
   hipError_t launch_pack_##suf(const double*, int, int, int, void*, void*, void*, void*, void*, \
                                void*, hipStream_t);
 BEST_DECL_PREC(f64)
@@ -43,20 +42,11 @@ hipError_t launch_eval(int prec, int MT, const KArgs& a, int grid, size_t lds, h
     default: return launch_eval_bf16(MT, a, grid, lds, s);
   }
 }
-hipError_t launch_train_tile(int prec, int MT, const TrainArgs& a, int grid, size_t lds,
-                             hipStream_t s) {
+hipError_t launch_fit(int prec, const FitArgs& a, hipStream_t s) {
   switch (prec) {
-    case BEST_FP32: return launch_train_tile_f32(MT, a, grid, lds, s);
-    case BEST_FP16: return launch_train_tile_f16(MT, a, grid, lds, s);
-    case BEST_BF16: return launch_train_tile_bf16(MT, a, grid, lds, s);
-    default: return hipErrorInvalidValue;
-  }
-}
-hipError_t launch_vjp(int prec, int MT, const VjpArgs& a, int grid, size_t lds, hipStream_t s) {
-  switch (prec) {
-    case BEST_FP32: return launch_vjp_f32(MT, a, grid, lds, s);
-    case BEST_FP16: return launch_vjp_f16(MT, a, grid, lds, s);
-    case BEST_BF16: return launch_vjp_bf16(MT, a, grid, lds, s);
+    case BEST_FP32: return launch_fit_f32(a, s);
+    case BEST_FP16: return launch_fit_f16(a, s);
+    case BEST_BF16: return launch_fit_bf16(a, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -104,6 +94,36 @@ struct Arena {
   void free_all() {
     for (void* p : ptrs) (void)hipFree(p);
     ptrs.clear();
+  }
+};
+
+// Buffers of a layer-by-layer forward and reverse pass over up to `cap` points (a multiple of
+// 16): (2 nh + 2) H + d + 1 floats per point (the panels 2 H 16-bit values for those types).
+struct FitBufs {
+  float *act = nullptr, *hx = nullptr, *th = nullptr, *up = nullptr;
+  char *pp0 = nullptr, *pp1 = nullptr;
+  int64_t cap = 0;
+  bool reserve(Arena& m, int prec, int d, int H, int nh, int64_t ldb) {
+    if (ldb <= cap) return true;
+    for (void* q : {(void*)act, (void*)hx, (void*)th, (void*)up, (void*)pp0, (void*)pp1}) m.release(q);
+    *this = FitBufs{};
+    const size_t rows = (size_t)nh * H, panel = (size_t)H * tsize(prec);
+    if (m.alloc(&act, rows * ldb) != hipSuccess || m.alloc(&hx, rows * ldb) != hipSuccess ||
+        m.alloc(&th, (size_t)d * ldb) != hipSuccess || m.alloc(&up, (size_t)ldb) != hipSuccess ||
+        m.alloc(&pp0, panel * ldb) != hipSuccess || m.alloc(&pp1, panel * ldb) != hipSuccess)
+      return false;
+    cap = ldb;
+    return true;
+  }
+  void fill(FitArgs& a, int64_t n) const {
+    a.n = n;
+    a.ldb = (n + 15) / 16 * 16;
+    a.act = act;
+    a.hx = hx;
+    a.th = th;
+    a.up = up;
+    a.pp0 = pp0;
+    a.pp1 = pp1;
   }
 };
 
@@ -169,8 +189,7 @@ struct best_ctx {
   size_t ev_hsave_bytes = 0;
   bool mult_on = false;
   // weight-gradient (vector-Jacobian product) buffers, allocated by the first call
-  float *vj_h = nullptr, *vj_dl = nullptr, *vj_th = nullptr, *vj_up = nullptr;
-  int64_t vj_cap = 0;
+  FitBufs vj;
   int64_t* vj_offs = nullptr;
   NutsState nu{};
   std::vector<double> lower, upper;
@@ -654,47 +673,23 @@ int best_logL_param_grad(best_ctx* h, const double* x, int64_t n, const double* 
   }
   if (h->prec == BEST_FP64)
     return fail(h, BEST_ESTATE, "the parameter gradient needs FP32, FP16 or BF16 precision");
-  const int64_t ldb = (n + 15) / 16 * 16;
-  if (ldb > h->vj_cap) {
-    for (void* q : {(void*)h->vj_h, (void*)h->vj_dl, (void*)h->vj_th, (void*)h->vj_up})
-      h->mem.release(q);
-    h->vj_h = h->vj_dl = h->vj_th = h->vj_up = nullptr;
-    h->vj_cap = 0;
-    const size_t rows = (size_t)h->nh * h->H;
-    if (h->mem.alloc(&h->vj_h, rows * ldb) != hipSuccess ||
-        h->mem.alloc(&h->vj_dl, rows * ldb) != hipSuccess ||
-        h->mem.alloc(&h->vj_th, (size_t)h->d * ldb) != hipSuccess ||
-        h->mem.alloc(&h->vj_up, (size_t)ldb) != hipSuccess)
-      return fail(h, BEST_ENOMEM, "parameter-gradient buffers");
-    h->vj_cap = ldb;
-  }
+  if (!h->vj.reserve(h->mem, h->prec, h->d, h->H, h->nh, (n + 15) / 16 * 16))
+    return fail(h, BEST_ENOMEM, "parameter-gradient buffers");
   if (!h->vj_offs) {
     std::vector<int64_t> offs;
     param_offsets(h->d, h->H, h->nh, offs);
     HIPCHK(h, h->mem.upload(&h->vj_offs, offs.data(), offs.size(), h->stream));
   }
-  VjpArgs a{};
+  FitArgs a{};
+  a.mp = h->mp;
+  a.round_h = h->lds_h;
   a.tg = h->tg;
   a.tg.mlp_coef = h->mlp_coef;
-  a.mp = h->mp;
-  a.lds = h->lds;
   a.x = x;
-  a.pitch = n;
-  a.n = n;
-  a.ldb = ldb;
-  const int64_t M = 16 * h->MT;
-  a.n_tiles = (n + M - 1) / M;
   a.upstream = upstream;
-  a.hsave = h->hsave;
-  a.hsave_stride = h->hsave_stride;
-  a.ex_h = h->vj_h;
-  a.ex_dl = h->vj_dl;
-  a.ex_th = h->vj_th;
-  a.ex_up = h->vj_up;
-  const int grid = (int)std::min<int64_t>(a.n_tiles, h->grid_cap);
-  HIPCHK(h, launch_vjp(h->prec, h->MT, a, grid, h->lds.total, h->stream));
-  HIPCHK(h, launch_dw(h->vj_dl, h->vj_h, h->vj_th, h->vj_up, ldb, h->d, h->H, h->nh,
-                      grad_params, h->vj_offs, h->stream));
+  h->vj.fill(a, n);
+  HIPCHK(h, launch_fit(h->prec, a, h->stream));
+  HIPCHK(h, launch_dw(a, grad_params, h->vj_offs, h->stream));
   return BEST_OK;
 }
 
@@ -1462,19 +1457,15 @@ struct best_trainer {
   std::string err;
   hipStream_t stream = nullptr;
   int n_cu = 256;
-  int d = 0, H = 0, nh = 0, prec = BEST_FP32, MT = 2;
+  int d = 0, H = 0, nh = 0, prec = BEST_FP32;
   int64_t np = 0, t = 0;
   Arena mem;
   double *p = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;
   void *wf = nullptr, *wb = nullptr, *w1f = nullptr, *w1t = nullptr, *bias = nullptr,
        *wout = nullptr;
   MlpParams mp{};
-  LdsLayout lds{};
-  void* hsave = nullptr;
-  int64_t hsave_stride = 0;
-  int grid_cap = 0;
   int64_t bcap = 0;
-  float *ex_h = nullptr, *ex_dl = nullptr, *ex_th = nullptr, *ex_up = nullptr;
+  FitBufs bufs;
   double *loss_part = nullptr, *loss_steps = nullptr;
   int64_t ls_cap = 0;
   int32_t* ident = nullptr;
@@ -1493,16 +1484,11 @@ static int tfail(best_trainer* t, int code, const std::string& msg) {
 
 static int trainer_buffers(best_trainer* t, int64_t B) {
   if (B <= t->bcap) return BEST_OK;
-  for (void* q : {(void*)t->ex_h, (void*)t->ex_dl, (void*)t->ex_th, (void*)t->ex_up,
-                  (void*)t->loss_part, (void*)t->ident})
-    t->mem.release(q);
+  t->mem.release(t->loss_part);
+  t->mem.release(t->ident);
   t->bcap = 0;
-  const int64_t M = 16 * t->MT;
-  if (t->mem.alloc(&t->ex_h, (size_t)t->nh * t->H * B) != hipSuccess ||
-      t->mem.alloc(&t->ex_dl, (size_t)t->nh * t->H * B) != hipSuccess ||
-      t->mem.alloc(&t->ex_th, (size_t)t->d * B) != hipSuccess ||
-      t->mem.alloc(&t->ex_up, (size_t)B) != hipSuccess ||
-      t->mem.alloc(&t->loss_part, (size_t)(B + M - 1) / M) != hipSuccess ||
+  if (!t->bufs.reserve(t->mem, t->prec, t->d, t->H, t->nh, B) ||
+      t->mem.alloc(&t->loss_part, (size_t)B / 16) != hipSuccess ||
       t->mem.alloc(&t->ident, (size_t)B) != hipSuccess)
     return tfail(t, BEST_ENOMEM, "training buffers");
   std::vector<int32_t> id(B);
@@ -1516,28 +1502,18 @@ static int trainer_buffers(best_trainer* t, int64_t B) {
 // Forward + backward over one minibatch and the weight gradients into t->g.
 static int trainer_grad(best_trainer* t, const float* t_in, const float* y, const int32_t* perm,
                         int64_t batch0, int64_t B, double* loss_out_dev) {
-  TrainArgs a{};
+  FitArgs a{};
   a.mp = t->mp;
-  a.lds = t->lds;
+  a.round_h = t->mp.lds_h;
   a.t_in = t_in;
   a.y = y;
   a.perm = perm;
   a.batch0 = batch0;
-  a.B = B;
-  const int64_t M = 16 * t->MT;
-  a.n_tiles = (B + M - 1) / M;
-  a.hsave = t->hsave;
-  a.hsave_stride = t->hsave_stride;
-  a.ex_h = t->ex_h;
-  a.ex_dl = t->ex_dl;
-  a.ex_th = t->ex_th;
-  a.ex_up = t->ex_up;
   a.loss_part = t->loss_part;
-  const int grid = (int)std::min<int64_t>(a.n_tiles, t->grid_cap);
-  THIPCHK(t, launch_train_tile(t->prec, t->MT, a, grid, t->lds.total, t->stream));
-  THIPCHK(t, launch_dw(t->ex_dl, t->ex_h, t->ex_th, t->ex_up, B, t->d, t->H, t->nh, t->g,
-                       t->offs, t->stream));
-  THIPCHK(t, launch_sum(t->loss_part, (int)a.n_tiles, 1.0 / (double)B, loss_out_dev, t->stream));
+  t->bufs.fill(a, B);
+  THIPCHK(t, launch_fit(t->prec, a, t->stream));
+  THIPCHK(t, launch_dw(a, t->g, t->offs, t->stream));
+  THIPCHK(t, launch_sum(t->loss_part, (int)(B / 16), 1.0 / (double)B, loss_out_dev, t->stream));
   return BEST_OK;
 }
 
@@ -1570,11 +1546,13 @@ int best_trainer_create(best_trainer** out, int32_t d, int32_t width, int32_t n_
   if (he == hipSuccess) he = hipDeviceGetAttribute(&t->n_cu, hipDeviceAttributeMultiprocessorCount, dev);
   if (he != hipSuccess)
     return bail(tfail(t, BEST_EHIP, std::string("no usable HIP device: ") + hipGetErrorString(he)));
-  t->MT = 2;
-  while (t->MT > 1 && layout_for(precision, t->MT, width, d, n_hidden, 0).total > kLdsMax) t->MT /= 2;
-  const int lds_h = layout_for(precision, t->MT, width, d, n_hidden, 1).total <= kLdsMax ? 1 : 0;
-  t->lds = layout_for(precision, t->MT, width, d, n_hidden, lds_h);
-  if (t->lds.total > kLdsMax) return bail(tfail(t, BEST_EINVAL, "width too large for LDS"));
+  // whether the reverse pass takes the activations in the GEMM type: where tiles of 32 (16)
+  // points would hold them in LDS, as the tile engine does
+  int mt = 2;
+  while (mt > 1 && layout_for(precision, mt, width, d, n_hidden, 0).total > kLdsMax) mt /= 2;
+  if (layout_for(precision, mt, width, d, n_hidden, 0).total > kLdsMax)
+    return bail(tfail(t, BEST_EINVAL, "width too large for LDS"));
+  const int lds_h = layout_for(precision, mt, width, d, n_hidden, 1).total <= kLdsMax ? 1 : 0;
   if (!finite_all(init_params, t->np)) return bail(tfail(t, BEST_EINVAL, "init params must be finite"));
   const int ts = tsize(precision);
   const size_t nW = (size_t)std::max(n_hidden - 1, 1) * width * width;
@@ -1595,10 +1573,6 @@ int best_trainer_create(best_trainer** out, int32_t d, int32_t width, int32_t n_
     return bail(tfail(t, BEST_EHIP, "memset"));
   t->mp = make_mlp_params(precision, d, width, n_hidden, lds_h, t->wf, t->wb, t->w1f, t->w1t,
                           t->bias, t->wout);
-  t->grid_cap = t->n_cu * std::max(1, std::min(2, kLdsMax / t->lds.total));
-  t->hsave_stride = (int64_t)n_hidden * width * 16 * t->MT;
-  if (t->mem.alloc((char**)&t->hsave, (size_t)t->grid_cap * t->hsave_stride * 4) != hipSuccess)
-    return bail(tfail(t, BEST_ENOMEM, "activation scratch"));
   // gradient offsets: [W1, b1, b2..b_nh, w_out, b_out]
   std::vector<int64_t> offs;
   param_offsets(d, width, n_hidden, offs);

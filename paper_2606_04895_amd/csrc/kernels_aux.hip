@@ -402,23 +402,22 @@ __global__ void adam_kernel(double* p, double* m, double* v, const double* g, in
 // after them: dW_1, the biases, w_out and b_out as FP64 sums over the batch.
 //
 // GEMM blocks.  Each wave owns R x R tiles of 16 x 16 outputs and walks the whole batch, so
-// every output has one accumulator whose order does not depend on R.  The operands are rows
-// of the exported arrays (16 bytes per lane, 64 bytes per row and k-step) loaded kDwRing
-// k-steps ahead straight into fragments: at R = 2 a wave loads 4 KiB per 512 MFMA cycles,
-// 32 B per clock and CU, below what L2 delivers, so LDS staging would only add barriers.  The
-// bound is the FP32 matrix rate at R = 2 and the serial accumulator chain (128 cycles per 16
-// points) at R = 1.  Measured for 512 x 4 layers and 1024 points: 15 us in this launch, against
-// 3 x 39 us (one launch per layer, no loads ahead) plus 172 us (a thread per small output,
-// serial and uncoalesced over the batch).
+// every output has one accumulator whose order does not depend on R.  Both operands lie in
+// fragment order (1 KiB contiguous per fragment) and are loaded kDwRing k-steps ahead: at
+// R = 2 a wave loads 4 KiB per 512 MFMA cycles, 32 B per clock and CU, below what L2 delivers,
+// so LDS staging would only add barriers.  The bound is the FP32 matrix rate at R = 2 and the
+// serial accumulator chain (128 cycles per 16 points) at R = 1.  512 x 4 layers, 1024 points:
+// 20.4 us (13.7 us of MFMA); 35 us with the operands as rows of the batch (64 bytes per row, rows
+// 4 KiB apart on the same L2 channels) and the ring's loads issued together at its end.
 //
-// Small blocks.  One wave per row of delta_l (bias; for l = 1 also the d products with the
-// inputs, eight components at a time), of h_L (w_out) and one for b_out: rows are contiguous
-// in the batch, so the loads coalesce, and the lanes' FP64 sums are combined by a butterfly.
+// Small blocks.  One workgroup per 16 rows of delta_l (bias), of delta_1 and input component
+// (W_1), of h_L (w_out) and one for b_out; the waves split the batch and their FP64 sums are
+// combined in wave order.
 constexpr int kDwRing = 4;
 
 struct DwArgs {
-  const float *dl, *h, *th, *up;
-  int64_t ldb;  // batch columns (a multiple of 16)
+  const float *dl, *h, *th, *up;  // deltas and activations as blocks in weight-gradient order
+  int64_t ldb;
   int d, H, nh;
   double* grad;
   const int64_t* offs;  // [W1, b1, b2 .. b_nh, w_out, b_out] offsets into grad (nh + 3)
@@ -426,70 +425,68 @@ struct DwArgs {
   int n_gemm;
 };
 
-__device__ __forceinline__ double lanes_sum(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+// FP64 sum over the batch of f(column tile) per row of a 16-row block: lane (q, r) of each wave
+// adds its points of row r, then lanes q and the waves; valid in lanes 0 .. 15 of wave 0.
+constexpr int kDwWaves = kAuxThreads / 64;
+template <class F>
+__device__ __forceinline__ double dw_rows(int64_t CT, double (*sh)[16], const F& f) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  double s = 0;
+#pragma unroll 4
+  for (int64_t ct = wv; ct < CT; ct += kDwWaves) s += f(ct);
+  s = sum_lane_groups(s);
+  __syncthreads();
+  if (lane < 16) sh[wv][lane] = s;
+  __syncthreads();
+  s = 0;
+  for (int w = 0; w < kDwWaves; ++w) s += sh[w][lane & 15];
+  return s;
 }
 
-__device__ __forceinline__ void dw_small(const DwArgs& a, int64_t row) {
-  const int lane = threadIdx.x & 63;
-  const int64_t nrow = (int64_t)a.nh * a.H;
-  const int64_t nq = a.ldb / 4;
-  const f32x4* __restrict__ up4 = (const f32x4*)a.up;
-  if (row < nrow) {
-    const f32x4* __restrict__ x = (const f32x4*)(a.dl + row * a.ldb);
-    const int l = (int)(row / a.H), j = (int)(row % a.H);
-    double s = 0;
-#pragma unroll 2
-    for (int64_t q = lane; q < nq; q += 64) {
-      const f32x4 v = x[q];
-      s += ((double)v[0] + (double)v[1]) + ((double)v[2] + (double)v[3]);
-    }
-    s = lanes_sum(s);
-    if (lane == 0) a.grad[a.offs[1 + l] + j] = s;
-    if (l > 0) return;
-    for (int i0 = 0; i0 < a.d; i0 += 8) {
-      double p[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-      for (int64_t q = lane; q < nq; q += 64) {
-        const f32x4 v = x[q];
-        f32x4 t[8];
+__device__ __forceinline__ void dw_small(const DwArgs& a, int b) {
+  __shared__ double sh[kDwWaves][16];
+  const int lane = threadIdx.x & 63, q = lane >> 4, RT = a.H / 16;
+  const int64_t CT = a.ldb / 16;
+  const bool own = threadIdx.x < 16;
+  const f32x4* __restrict__ up = (const f32x4*)a.up + q;
+  if (b < a.nh * RT) {
+    const int l = b / RT, rt = b % RT, j = rt * 16 + (lane & 15);
+    const f32x4* __restrict__ x = (const f32x4*)a.dl + ((int64_t)l * CT * RT + rt) * 64 + lane;
+    const double s = dw_rows(CT, sh, [&](int64_t ct) {
+      const f32x4 v = x[ct * RT * 64];
+      return ((double)v[0] + (double)v[1]) + ((double)v[2] + (double)v[3]);
+    });
+    if (own) a.grad[a.offs[1 + l] + j] = s;
+  } else if ((b -= a.nh * RT) < a.d * RT) {
+    const int i = b / RT, rt = b % RT;
+    const f32x4* __restrict__ x = (const f32x4*)a.dl + (int64_t)rt * 64 + lane;
+    const f32x4* __restrict__ t = (const f32x4*)(a.th + i * a.ldb) + q;
+    const double s = dw_rows(CT, sh, [&](int64_t ct) {
+      const f32x4 v = x[ct * RT * 64], u = t[ct * 4];
+      double p = 0;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int i = i0 + u < a.d ? i0 + u : a.d - 1;
-          t[u] = *(const f32x4*)(a.th + (int64_t)i * a.ldb + 4 * q);
-        }
+      for (int r = 0; r < 4; ++r) p += (double)v[r] * u[r];
+      return p;
+    });
+    if (own) a.grad[a.offs[0] + (int64_t)(rt * 16 + lane) * a.d + i] = s;
+  } else if ((b -= a.d * RT) < RT) {
+    const int rt = b;
+    const f32x4* __restrict__ x =
+        (const f32x4*)a.h + ((int64_t)(a.nh - 1) * CT * RT + rt) * 64 + lane;
+    const double s = dw_rows(CT, sh, [&](int64_t ct) {
+      const f32x4 v = x[ct * RT * 64], u = up[ct * 4];
+      double p = 0;
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) p[u] += (double)v[r] * t[u][r];
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const double w = lanes_sum(p[u]);
-        if (lane == 0 && i0 + u < a.d) a.grad[a.offs[0] + (int64_t)j * a.d + i0 + u] = w;
-      }
-    }
-  } else if (row < nrow + a.H) {
-    const int64_t j = row - nrow;
-    const f32x4* __restrict__ x = (const f32x4*)(a.h + (nrow - a.H + j) * a.ldb);
-    double s = 0;
-#pragma unroll 2
-    for (int64_t q = lane; q < nq; q += 64) {
-      const f32x4 v = x[q], u = up4[q];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) s += (double)u[r] * v[r];
-    }
-    s = lanes_sum(s);
-    if (lane == 0) a.grad[a.offs[1 + a.nh] + j] = s;
-  } else if (row == nrow + a.H) {
-    double s = 0;
-    for (int64_t q = lane; q < nq; q += 64) {
-      const f32x4 u = up4[q];
-      s += ((double)u[0] + (double)u[1]) + ((double)u[2] + (double)u[3]);
-    }
-    s = lanes_sum(s);
-    if (lane == 0) a.grad[a.offs[2 + a.nh]] = s;
+      for (int r = 0; r < 4; ++r) p += (double)u[r] * v[r];
+      return p;
+    });
+    if (own) a.grad[a.offs[1 + a.nh] + rt * 16 + lane] = s;
+  } else {
+    const double s = dw_rows(CT, sh, [&](int64_t ct) {
+      const f32x4 u = up[ct * 4];
+      return ((double)u[0] + (double)u[1]) + ((double)u[2] + (double)u[3]);
+    });
+    if (threadIdx.x == 0) a.grad[a.offs[2 + a.nh]] = s;
   }
 }
 
@@ -497,34 +494,31 @@ template <int R>
 __global__ __launch_bounds__(kAuxThreads) void dw_kernel(DwArgs a) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane >> 4, cl = lane & 15;
   if ((int)blockIdx.x >= a.n_gemm) {
-    dw_small(a, (int64_t)(blockIdx.x - a.n_gemm) * (kAuxThreads / 64) + wv);
+    dw_small(a, blockIdx.x - a.n_gemm);
     return;
   }
-  // blocks b, b + 8, ... run on one XCD: give each XCD a contiguous run of tiles, so that its L2
-  // holds the rows they share
-  constexpr int TS = 32 * R;  // block tile
-  const int nt = a.H / TS, per = nt * nt;
-  int b = blockIdx.x;
-  if (a.n_gemm % 8 == 0) b = (b % 8) * (a.n_gemm / 8) + b / 8;
+  constexpr int TB = 2 * R;  // block tile in 16 x 16 outputs
+  const int RT = a.H / 16, nt = RT / TB, per = nt * nt;
+  const int b = xcd_run(blockIdx.x, a.n_gemm);
   const int l = b / per, t = b % per;
-  const int r0 = (t / nt) * TS + (wv >> 1) * 16 * R, k0 = (t % nt) * TS + (wv & 1) * 16 * R;
-  const int64_t ldb = a.ldb, HB = (int64_t)a.H * ldb;
-  const f32x4* __restrict__ A = (const f32x4*)(a.dl + (l + 1) * HB + (r0 + cl) * ldb) + g;
-  const f32x4* __restrict__ Bp = (const f32x4*)(a.h + l * HB + (k0 + cl) * ldb) + g;
-  const int64_t rs = 16 * ldb / 4;  // one row tile further, in fragments
-  const int64_t ns = ldb / 16;      // k-steps
+  const int r0 = (t / nt) * TB + (wv >> 1) * R, k0 = (t % nt) * TB + (wv & 1) * R;
+  const int64_t ns = a.ldb / 16;           // k-steps
+  const int64_t st = (int64_t)RT * 64;     // fragments per k-step
+  const f32x4* __restrict__ A = (const f32x4*)a.dl + ((l + 1) * ns * RT + r0) * 64 + lane;
+  const f32x4* __restrict__ B = (const f32x4*)a.h + (l * ns * RT + k0) * 64 + lane;
   f32x4 acc[R][R] = {};
   f32x4 fa[kDwRing][R], fb[kDwRing][R];
-  auto load = [&](int p, int64_t s) {
-    const int64_t o = 4 * (s < ns ? s : ns - 1);
+  int64_t next = 0, o = 0;  // the k-step loaded next (the last one again past the end)
+  auto load = [&](int p) {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      fa[p][r] = A[r * rs + o];
-      fb[p][r] = Bp[r * rs + o];
+      fa[p][r] = A[r * 64 + o];
+      fb[p][r] = B[r * 64 + o];
     }
+    if (++next < ns) o += st;
   };
 #pragma unroll
-  for (int p = 0; p < kDwRing; ++p) load(p, p);
+  for (int p = 0; p < kDwRing; ++p) load(p);
   auto mma = [&](int p) {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
@@ -540,7 +534,8 @@ __global__ __launch_bounds__(kAuxThreads) void dw_kernel(DwArgs a) {
 #pragma unroll
     for (int p = 0; p < kDwRing; ++p) {
       mma(p);
-      load(p, s0 + p + kDwRing);
+      load(p);
+      __builtin_amdgcn_sched_barrier(0);  // else every load of the ring is issued at its end
     }
   }
 #pragma unroll
@@ -553,7 +548,7 @@ __global__ __launch_bounds__(kAuxThreads) void dw_kernel(DwArgs a) {
     for (int j = 0; j < R; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        gW[(int64_t)(r0 + 16 * i + 4 * g + r) * a.H + k0 + 16 * j + cl] = (double)acc[i][j][r];
+        gW[(int64_t)((r0 + i) * 16 + 4 * g + r) * a.H + (k0 + j) * 16 + cl] = (double)acc[i][j][r];
 }
 
 __global__ void sum_kernel(const double* part, int n, double scale, double* out) {
@@ -727,19 +722,25 @@ hipError_t launch_adam(double* p, double* m, double* v, const double* g, int64_t
   return hipGetLastError();
 }
 
-hipError_t launch_dw(const float* dl, const float* h, const float* th, const float* up,
-                     int64_t B, int d, int H, int nh, double* grad, const int64_t* offs,
-                     hipStream_t s) {
-  DwArgs a{dl, h, th, up, B, d, H, nh, grad, offs, (int64_t)H * d + H, (int64_t)H * H + H, 0};
-  const int64_t rows = (int64_t)nh * H + H + 1, waves = kAuxThreads / 64;
-  const int64_t small = (rows + waves - 1) / waves;
+hipError_t launch_dw(const FitArgs& f, double* grad, const int64_t* offs, hipStream_t s) {
+  const int d = f.mp.d, H = f.mp.H, nh = f.mp.nh;
+  DwArgs a{f.act, f.hx, f.th, f.up, f.ldb, d, H, nh, grad, offs, (int64_t)H * d + H,
+           (int64_t)H * H + H, 0};
+  const int64_t small = (int64_t)(nh + d + 1) * (H / 16) + 1;
   // 2 x 2 tiles per wave once that still gives half of the chip's 1024 SIMDs a wave (each
   // operand load then serves two MFMAs; 512 x 4 layers: 768 waves); below, one tile per wave,
   // which four times as many SIMDs share (128 x 2 and 1024 points: 16 waves against 64)
   const int64_t tiles = (int64_t)(nh - 1) * (H / 16) * (H / 16);
   if (tiles / 4 >= 512) {
     a.n_gemm = (int)(tiles / 16);
-    hipLaunchKernelGGL((dw_kernel<2>), dim3((unsigned)(a.n_gemm + small)), dim3(kAuxThreads), 0, s, a);
+    // GEMM blocks that do not fill the 256 CUs ask for more than half of a CU's LDS: one block
+    // per CU, so the small blocks run on the other CUs instead of beside GEMM waves (512 x 4
+    // layers, 1024 points: 20.4 us against 24.7)
+    const size_t lds = a.n_gemm <= 256 ? 84 * 1024 : 0;
+    hipError_t e = hipFuncSetAttribute((const void*)dw_kernel<2>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, 84 * 1024);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((dw_kernel<2>), dim3((unsigned)(a.n_gemm + small)), dim3(kAuxThreads), lds, s, a);
   } else {
     a.n_gemm = (int)(tiles / 4);
     hipLaunchKernelGGL((dw_kernel<1>), dim3((unsigned)(a.n_gemm + small)), dim3(kAuxThreads), 0, s, a);

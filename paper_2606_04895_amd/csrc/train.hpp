@@ -1,5 +1,7 @@
-// Templated kernels for weight packing and emulator training (forward + MSE upstream +
-// backward for one chain tile of the minibatch, exporting activations and deltas).
+// Templated kernels for weight packing and for the passes that need weight gradients (emulator
+// training and the vector-Jacobian product of the target): layer-by-layer forward and reverse
+// passes over a batch that leave every activation and delta in the weight-gradient GEMMs'
+// operand order.
 #pragma once
 #include "kernels.hpp"
 
@@ -59,145 +61,311 @@ __global__ void pack_kernel(const double* flat, int d, int H, int nh, typename P
   }
 }
 
-struct TrainArgs {
+// ---------------------------------------------------------------------------------------
+// Forward and reverse pass over a batch, one launch per layer.
+//
+// A tile that goes through all layers in one workgroup (the samplers' form) leaves most of the
+// chip idle on a minibatch: 1024 points are 64 tiles of 16.  Here each layer is a GEMM over the
+// whole batch whose 16 x 16 output tiles are spread over the chip (2048 tiles for 512 x 1024),
+// and a layer costs about one kernel (FP32, 512 x 512 x 1024: 7 us, of which 3.4 us are MFMA and
+// the rest launch, first-touch latency and epilogue).  512 x 4 layers: the passes of a training
+// step of 1024 points in FP32 took 272 us as one launch of 32-point tiles and take 56 us here;
+// 4099 points in FP16 153 us and 83 us.
+//
+// Buffers are in units of 16 x 16 blocks (row tile rt, column tile ct = 16 points), block
+// (layer, ct, rt) at ((layer * CT + ct) * RT + rt) * 256 floats:
+//   act  h_l in D-slot order (lane (g, c): rows 4g .. 4g + 3 of point c), which for FP32 is also
+//        the B operand of the next layer.  Each block is overwritten by delta_l (in the order of
+//        hx) by the wave that read it last, so the two share the memory.
+//   hx   h_l in the weight-gradient order: lane (q, r) holds points 4q .. 4q + 3 of row r.
+//   pp   two panels [CT][16 H] of the GEMM type in B-fragment order: the 16-bit activations of
+//        the layer just computed in the forward pass, the deltas in the reverse pass.
+// Every output keeps the accumulation order of the tile engine (one accumulator per output,
+// k-steps ascending), and the sums over the output weights its wave order, so the results are
+// those of the tile engine bit for bit.
+// ---------------------------------------------------------------------------------------
+struct FitArgs {
   MlpParams mp;
-  LdsLayout lds;
-  const float* t_in;
-  const float* y;
+  int64_t n, ldb;   // points, and points rounded up to whole column tiles
+  int round_h;      // the reverse pass takes h_l rounded to the GEMM type
+  // training minibatch: rows perm[batch0 ..] of t_in [.][d] with targets y
+  const float *t_in, *y;
   const int32_t* perm;
-  int64_t batch0, B, n_tiles;
-  void* hsave;
-  int64_t hsave_stride;
-  float *ex_h, *ex_dl, *ex_th, *ex_up;
-  double* loss_part;
+  int64_t batch0;
+  double* loss_part;  // [CT] sums of squared residuals
+  // target points x [d][n] (t_in == nullptr): upstream weights (NULL: ones) times mlp_coef, zero
+  // for points whose log pi does not use the network
+  Target tg;
+  const double *x, *upstream;
+  float *act, *hx;  // [nh] blocks
+  float *th, *up;   // [d][ldb], [ldb]
+  void *pp0, *pp1;
 };
 
-template <class P, int MT>
-__global__ __launch_bounds__(kThreads, 1) void train_tile_kernel(TrainArgs a) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  using acc = typename P::acc;
-  using vec = typename P::vec;
-  using IP = typename InPrec<P>::type;
-  constexpr int M = 16 * MT;
-  const int tid = local_tid(), d = a.mp.d, K1 = a.mp.ks1 * IP::KSTEP;
-  acc* hsave = (acc*)a.hsave + (int64_t)blockIdx.x * a.hsave_stride;
-  MlpSmem<P> s = mlp_smem<P, MT>(smem + a.lds.big, a.mp);
-  s.thf = (typename IP::T*)(smem + a.lds.th);
-  s.gth = (vec*)(smem + a.lds.gth);
-  s.red = (acc*)(smem + a.lds.red);
-  s.outp = (acc*)(smem + a.lds.outp);
-  s.out = (acc*)(smem + a.lds.out);
-  s.up = (acc*)(smem + a.lds.up);
-  double* r2 = (double*)(smem + a.lds.md);
-  for (int64_t tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
-    const int64_t c0 = tile * M;
-    const int mv = (int)((a.B - c0) < M ? (a.B - c0) : M);
-    for (int e = tid; e < M * K1; e += kThreads) {
-      const int c = e / K1, i = e % K1;
+// Launch index -> tile index such that the blocks of one XCD (index mod 8) own a contiguous run
+// of tiles, whose shared operands then stay in that XCD's L2.
+__device__ __forceinline__ int xcd_run(int b, int n) {
+  const int x = b & 7, q = n >> 3, r = n & 7;
+  return x * q + (x < r ? x : r) + (b >> 3);
+}
+
+// Transpose of the 4 x 4 blocks (4 consecutive lanes x 4 values): in lane i of a quad, v[j]
+// becomes the former v[i] of lane j.
+__device__ __forceinline__ float quad_xor(float v, bool by2) {
+  const int b = __builtin_bit_cast(int, v);
+  return __builtin_bit_cast(float, by2 ? __builtin_amdgcn_mov_dpp(b, 0x4E, 0xF, 0xF, true)
+                                       : __builtin_amdgcn_mov_dpp(b, 0xB1, 0xF, 0xF, true));
+}
+__device__ __forceinline__ f32x4 quad_transpose(f32x4 v, int lane) {
+  const bool o1 = lane & 1, o2 = lane & 2;
+  const float a = quad_xor(o1 ? v[0] : v[1], false), b = quad_xor(o1 ? v[2] : v[3], false);
+  const f32x4 w = {o1 ? a : v[0], o1 ? v[1] : a, o1 ? b : v[2], o1 ? v[3] : b};
+  const float c = quad_xor(o2 ? w[0] : w[2], true), e = quad_xor(o2 ? w[1] : w[3], true);
+  return f32x4{o2 ? c : w[0], o2 ? e : w[1], o2 ? w[2] : c, o2 ? w[3] : e};
+}
+
+// Slot of a D-order lane's transposed values in the weight-gradient order.
+__device__ __forceinline__ int dw_slot(int lane) {
+  return ((lane & 15) >> 2) * 16 + (lane >> 4) * 4 + (lane & 3);
+}
+
+__device__ __forceinline__ int64_t fit_block(const FitArgs& a, int l, int64_t ct, int rt) {
+  return (((int64_t)l * (a.ldb >> 4) + ct) * (a.mp.H >> 4) + rt) * 64;
+}
+
+// The four rows of a D-slot as one column-tile panel entry of the GEMM type.  The values are
+// rounded to FP32 first: folded into one instruction, the FP16 conversion of 1 - 2 rcp(..) would
+// skip that rounding and differ from the tile engine's activations on ties.
+template <class P>
+__device__ __forceinline__ void panel_store(const FitArgs& a, typename P::T* panel, int64_t ct,
+                                            int rt, int lane, f32x4 v) {
+  typedef typename P::T t4 __attribute__((ext_vector_type(4)));
+  using T = typename P::T;
+  if constexpr (sizeof(T) == 2) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float f = v[r];
+      asm volatile("" : "+v"(f));
+      v[r] = f;
+    }
+  }
+  const int64_t o = lds_off<P>(rt * 16 + 4 * (lane >> 4), lane & 15, a.mp.H / P::KSTEP);
+  *(t4*)(panel + ct * 16 * a.mp.H + o) = t4{(T)v[0], (T)v[1], (T)v[2], (T)v[3]};
+}
+
+// Input layer, kInRows row tiles of one column tile per wave (bound by latency: d <= 32).
+constexpr int kInRows = 2;
+template <class P>
+__global__ __launch_bounds__(256) void fit_input_kernel(FitArgs a) {
+  using IP = Prec<float>;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane >> 4, cl = lane & 15;
+  const int d = a.mp.d, ks1 = a.mp.ks1;
+  const int64_t ct = blockIdx.x, c = ct * 16 + cl;
+  const bool valid = c < a.n;
+  const bool lead = blockIdx.y == 0 && wv == 0;
+  const int64_t src = valid ? (a.t_in ? (int64_t)a.perm[a.batch0 + c] : c) : 0;
+  f32x4 b[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = ks * 16 + 4 * g + r;
       float v = 0.f;
-      if (c < mv && i < d) {
-        v = a.t_in[(int64_t)a.perm[a.batch0 + c0 + c] * d + i];
-        a.ex_th[(int64_t)i * a.B + c0 + c] = v;
-      }
-      store_t<P>(s, a.mp, c, i, v);
+      if (valid && i < d)
+        v = a.t_in ? a.t_in[src * d + i]
+                   : (float)((a.x[i * a.n + c] - a.tg.in_center[i]) * a.tg.in_invscale[i]);
+      b[ks][r] = v;
+      if (lead && i < d) a.th[(int64_t)i * a.ldb + c] = v;
     }
-    MlpExport ex{a.ex_h, a.ex_dl, a.B, c0, mv};
-    mlp_forward<P, MT>(a.mp, s, hsave, &ex, false, true, false);
-    if (tid < M) {
-      double r = 0;
-      if (tid < mv) r = (double)s.out[tid] - (double)a.y[a.perm[a.batch0 + c0 + tid]];
-      const acc u = (acc)(2.0 * r / (double)a.B);
-      s.up[tid] = u;
-      if (tid < mv) a.ex_up[c0 + tid] = (float)u;
-      r2[tid] = r * r;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      double t = 0;
-      for (int c = 0; c < M; ++c) t += r2[c];
-      a.loss_part[tile] = t;
-    }
-    mlp_backward<P, MT>(a.mp, s, hsave, &ex, false, false, false);
+  const f32x4* __restrict__ W = (const f32x4*)a.mp.w1f + lane;
+  const float* __restrict__ bias = (const float*)a.mp.bias;
+#pragma unroll
+  for (int rr = 0; rr < kInRows; ++rr) {
+    const int rt = (blockIdx.y * 4 + wv) * kInRows + rr;
+    const f32x4 bi = *(const f32x4*)(bias + rt * 16 + 4 * g);
+    f32x4 v = {};
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+      if (ks < ks1) v = IP::mma(W[((int64_t)rt * ks1 + ks) * 64], b[ks], v);
+    f32x4 h;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) h[r] = act_tanh(v[r] + bi[r]);
+    const int64_t o = fit_block(a, 0, ct, rt);
+    ((f32x4*)a.act)[o + lane] = h;
+    ((f32x4*)a.hx)[o + dw_slot(lane)] = quad_transpose(h, lane);
+    if constexpr (sizeof(typename P::T) == 2)
+      panel_store<P>(a, (typename P::T*)a.pp0, ct, rt, lane, h);
   }
 }
 
-// Vector-Jacobian product of the target with respect to the MLP parameters: for points x
-// ([d][pitch] FP64) and upstream weights w_c, the tile exports what the weight-gradient GEMMs
-// need for sum_c w_c d log pi(x_c) / d theta: the normalised inputs t, the activations h_l,
-// the deltas of the reverse pass started from u_c = mlp_coef * w_c (zero for a point whose
-// log pi does not use the MLP: outside the training box with the plain fallback), and u.
-// Arrays are column-major in the point index with leading dimension ldb (n rounded up to 16);
-// the padding columns [n, ldb) are written as zeros so the GEMMs can run over ldb columns.
-struct VjpArgs {
-  Target tg;
-  MlpParams mp;
-  LdsLayout lds;
-  const double* x;
-  int64_t pitch, n, ldb, n_tiles;
-  const double* upstream;  // [n] or NULL (all ones)
-  void* hsave;
-  int64_t hsave_stride;
-  float *ex_h, *ex_dl, *ex_th, *ex_up;
-};
+// Hidden layer l (1 <= l < nh, activations counted from 0): forward h_l from h_{l-1}, or with
+// BWD delta_{l-1} from delta_l.  R x C blocks per wave, four waves down the rows of a workgroup; the
+// weights (1 KiB contiguous per fragment) and the panel fragments of the next kFitRing k-steps
+// are in flight.  With C = 2 and R = 1 (the 1024-wave split of 1024 points) a wave loads
+// 3 KiB per 256 FP32 MFMA cycles, 48 B per clock and CU with the panel shared through L1.
+constexpr int kFitRing = 4;
+template <class P, int R, int C, bool BWD>
+__global__ __launch_bounds__(256) void fit_layer_kernel(FitArgs a, int l) {
+  using T = typename P::T;
+  using frag = typename P::frag;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane >> 4;
+  const int H = a.mp.H, KS = H / P::KSTEP, RT = H / 16, nrow = RT / (4 * R);
+  const int64_t CT = a.ldb >> 4;
+  const int t = xcd_run(blockIdx.x, gridDim.x);
+  const int rt0 = ((t % nrow) * 4 + wv) * R;
+  const int64_t ct0 = (int64_t)(t / nrow) * C;
+  const T* Aw = (const T*)(BWD ? a.mp.wb : a.mp.wf) + (int64_t)(l - 1) * H * H;
+  const frag* __restrict__ A = (const frag*)Aw + (int64_t)rt0 * KS * 64 + lane;
+  const int par = (a.mp.nh - 1 - l) & 1;  // reverse pass: delta_{nh-1} is in pp0
+  const T* Bin;
+  if constexpr (BWD) Bin = (const T*)(par ? a.pp1 : a.pp0);
+  else if constexpr (sizeof(T) == 4) Bin = (const T*)a.act + (l - 1) * CT * 16 * H;
+  else Bin = (const T*)((l & 1) ? a.pp0 : a.pp1);
+  const frag* __restrict__ B[C];
+#pragma unroll
+  for (int j = 0; j < C; ++j) {
+    const int64_t ct = ct0 + j < CT ? ct0 + j : CT - 1;  // past the end: computed, not stored
+    B[j] = (const frag*)Bin + ct * KS * 64 + lane;
+  }
+  frag fa[kFitRing][R], fb[kFitRing][C];
+  auto load = [&](int p, int ks) {
+#pragma unroll
+    for (int i = 0; i < R; ++i) fa[p][i] = A[((int64_t)i * KS + ks) * 64];
+#pragma unroll
+    for (int j = 0; j < C; ++j) fb[p][j] = B[j][(int64_t)ks * 64];
+  };
+#pragma unroll
+  for (int p = 0; p < kFitRing; ++p) load(p, p);
+  f32x4 e[R][BWD ? C : 1];  // epilogue operands: bias, or the saved activations
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    if constexpr (BWD) {
+#pragma unroll
+      for (int j = 0; j < C; ++j) {
+        const int64_t ct = ct0 + j < CT ? ct0 + j : CT - 1;
+        e[i][j] = ((const f32x4*)a.act)[fit_block(a, l - 1, ct, rt0 + i) + lane];
+      }
+    } else {
+      e[i][0] = *(const f32x4*)((const float*)a.mp.bias + (int64_t)l * H + (rt0 + i) * 16 + 4 * g);
+    }
+  }
+  f32x4 acc[R][C] = {};
+  auto mma = [&](int p) {
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int j = 0; j < C; ++j) acc[i][j] = P::mma(fa[p][i], fb[p][j], acc[i][j]);
+  };
+  int k0 = 0;
+  for (; k0 < KS - kFitRing; k0 += kFitRing) {
+#pragma unroll
+    for (int p = 0; p < kFitRing; ++p) {
+      mma(p);
+      load(p, k0 + p + kFitRing);
+      __builtin_amdgcn_sched_barrier(0);  // else every load of the ring is issued at its end
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < kFitRing; ++p) mma(p);
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int j = 0; j < C; ++j) {
+      if (ct0 + j >= CT) continue;
+      f32x4 v;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if constexpr (BWD) {
+          const float h = a.round_h ? (float)(T)e[i][j][r] : e[i][j][r];
+          v[r] = acc[i][j][r] * (1.0f - h * h);
+        } else {
+          v[r] = act_tanh(acc[i][j][r] + e[i][0][r]);
+        }
+      }
+      const int64_t ct = ct0 + j;
+      if constexpr (BWD) {
+        if (l > 1) panel_store<P>(a, (T*)(par ? a.pp0 : a.pp1), ct, rt0 + i, lane, v);
+        ((f32x4*)a.act)[fit_block(a, l - 1, ct, rt0 + i) + dw_slot(lane)] = quad_transpose(v, lane);
+      } else {
+        const int64_t o = fit_block(a, l, ct, rt0 + i);
+        ((f32x4*)a.act)[o + lane] = v;
+        ((f32x4*)a.hx)[o + dw_slot(lane)] = quad_transpose(v, lane);
+        if constexpr (sizeof(T) == 2) {
+          if (l + 1 < a.mp.nh) panel_store<P>(a, (T*)((l & 1) ? a.pp1 : a.pp0), ct, rt0 + i, lane, v);
+        }
+      }
+    }
+}
 
-template <class P, int MT>
-__global__ __launch_bounds__(kThreads, 1) void vjp_tile_kernel(VjpArgs a) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  using acc = typename P::acc;
-  using vec = typename P::vec;
-  using IP = typename InPrec<P>::type;
-  constexpr int M = 16 * MT;
-  const Target& tg = a.tg;
-  const int tid = local_tid(), d = a.mp.d, H = a.mp.H, nh = a.mp.nh;
-  const int K1 = a.mp.ks1 * IP::KSTEP;
-  acc* hsave = (acc*)a.hsave + (int64_t)blockIdx.x * a.hsave_stride;
-  MlpSmem<P> s = mlp_smem<P, MT>(smem + a.lds.big, a.mp);
-  s.thf = (typename IP::T*)(smem + a.lds.th);
-  s.gth = (vec*)(smem + a.lds.gth);
-  s.red = (acc*)(smem + a.lds.red);
-  s.outp = (acc*)(smem + a.lds.outp);
-  s.out = (acc*)(smem + a.lds.out);
-  s.up = (acc*)(smem + a.lds.up);
-  for (int64_t tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
-    const int64_t c0 = tile * M;
-    const int mv = (int)((a.n - c0) < M ? (a.n - c0) : M);
-    for (int e = tid; e < M * K1; e += kThreads) {
-      const int c = e / K1, i = e % K1;
-      double v = 0.0;
-      if (c < mv && i < d) {
-        v = (a.x[(int64_t)i * a.pitch + c0 + c] - tg.in_center[i]) * tg.in_invscale[i];
-        a.ex_th[(int64_t)i * a.ldb + c0 + c] = (float)v;
-      }
-      store_t<P>(s, a.mp, c, i, v);
+// Network output, upstream gradient (training: 2 (out - y) / n and the loss; target points: the
+// weights) and delta_L = u w_out (1 - h_L^2) of one column tile per workgroup.  The output dot
+// product runs in the tile engine's order: wave w sums the rows of its H / waves share, lane groups
+// by butterfly, waves in order.
+template <class P>
+__global__ __launch_bounds__(kThreads) void fit_output_kernel(FitArgs a) {
+  __shared__ float outp[kWaves][16], ups[16];
+  __shared__ double r2[16];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, g = lane >> 4, cl = lane & 15;
+  const int H = a.mp.H, RTW = H / (16 * kWaves), L = a.mp.nh - 1;
+  const int64_t ct = blockIdx.x;
+  const float* __restrict__ Wo = (const float*)a.mp.wout;
+  f32x4* hL = (f32x4*)a.act + fit_block(a, L, ct, 0);
+  if (a.t_in) {
+    float po = 0;
+#pragma unroll 4
+    for (int rr = 0; rr < RTW; ++rr) {
+      const int rt = wv * RTW + rr;
+      const f32x4 wo = *(const f32x4*)(Wo + rt * 16 + 4 * g), h = hL[rt * 64 + lane];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) po += wo[r] * h[r];
     }
-    for (int c = tid; c < M; c += kThreads) {
-      acc u = 0;
-      if (c < mv) {
-        bool use = tg.plain_mode == 0;
-        if (tg.plain_mode == 1) {
-          use = true;
-          for (int i = 0; i < d; ++i) {
-            const double xv = a.x[(int64_t)i * a.pitch + c0 + c];
-            use = use && xv >= tg.train_lo[i] && xv <= tg.train_hi[i];
-          }
-        }
-        const double w = a.upstream ? a.upstream[c0 + c] : 1.0;
-        u = use ? (acc)(tg.mlp_coef * w) : (acc)0;
-        a.ex_up[c0 + c] = (float)u;
-      } else if (c0 + c < a.ldb) {
-        // padding column: zero in every exported array
-        a.ex_up[c0 + c] = 0.f;
-        for (int i = 0; i < d; ++i) a.ex_th[(int64_t)i * a.ldb + c0 + c] = 0.f;
-        for (int64_t r = 0; r < (int64_t)nh * H; ++r) {
-          a.ex_h[r * a.ldb + c0 + c] = 0.f;
-          a.ex_dl[r * a.ldb + c0 + c] = 0.f;
+    const float v = sum_lane_groups(po);
+    if (g == 0) outp[wv][cl] = v;
+    __syncthreads();
+  }
+  if (tid < 16) {
+    const int64_t c = ct * 16 + tid;
+    float u = 0.f;
+    double r = 0;
+    if (a.t_in) {
+      float o = outp[0][tid];
+      for (int w = 1; w < kWaves; ++w) o += outp[w][tid];
+      o = o + Wo[H];
+      if (c < a.n) r = (double)o - (double)a.y[a.perm[a.batch0 + c]];
+      u = (float)(2.0 * r / (double)a.n);
+    } else if (c < a.n) {
+      bool use = a.tg.plain_mode == 0;
+      if (a.tg.plain_mode == 1) {
+        use = true;
+        for (int i = 0; i < a.mp.d; ++i) {
+          const double xv = a.x[i * a.n + c];
+          use = use && xv >= a.tg.train_lo[i] && xv <= a.tg.train_hi[i];
         }
       }
-      s.up[c] = u;
+      u = use ? (float)(a.tg.mlp_coef * (a.upstream ? a.upstream[c] : 1.0)) : 0.f;
     }
-    MlpExport ex{a.ex_h, a.ex_dl, a.ldb, c0, mv};
-    mlp_forward<P, MT>(a.mp, s, hsave, &ex, false, true, false);
-    mlp_backward<P, MT>(a.mp, s, hsave, &ex, false, false, false);
+    ups[tid] = u;
+    a.up[c] = u;
+    r2[tid] = r * r;
+  }
+  __syncthreads();
+  if (a.t_in && tid == 0) {
+    double s = 0;
+    for (int c = 0; c < 16; ++c) s += r2[c];
+    a.loss_part[ct] = s;
+  }
+  const float u = ups[cl];
+  for (int rr = 0; rr < RTW; ++rr) {
+    const int rt = wv * RTW + rr;
+    const f32x4 wo = *(const f32x4*)(Wo + rt * 16 + 4 * g), h4 = hL[rt * 64 + lane];
+    f32x4 v;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float h = a.round_h ? (float)(typename P::T)h4[r] : h4[r];
+      v[r] = u * wo[r] * (1.0f - h * h);
+    }
+    if (L > 0) panel_store<P>(a, (typename P::T*)a.pp0, ct, rt, lane, v);
+    hL[rt * 64 + dw_slot(lane)] = quad_transpose(v, lane);
   }
 }
 

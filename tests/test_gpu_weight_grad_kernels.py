@@ -11,7 +11,8 @@ import pytest
 import torch
 
 import paper_2606_04895_amd as B
-from oracle import train as OTR
+from oracle import mlp as OM, target as OT, train as OTR
+from workloads import small_problem
 from workloads.synth import mlp_layout, xavier_mlp
 
 pytestmark = pytest.mark.gpu
@@ -42,3 +43,26 @@ def test_weight_gradients_at_the_edges(d, width, nh, batch):
         n = int(np.prod(shape))
         a, b = g[off:off + n], ref[off:off + n]
         assert np.abs(a - b).max() < 2e-5 * np.abs(b).max() + 1e-12, (name, np.abs(a - b).max())
+
+
+@pytest.mark.parametrize("prec,n", [
+    ("fp32", 4100),    # one row and two columns of blocks per wave, the last column alone
+    ("bf16", 8200),    # two by two, the last column alone
+    ("fp16", 32769),   # two by four, a last column of one point
+    ("fp16", 1),       # one block per wave, one point
+])
+def test_batch_passes_with_a_ragged_last_column(prec, n):
+    """Tolerance on the scale of the largest component: 2e-5 in FP32; with 16-bit layer inputs
+    (8 / 11 bits, rounding 2^-9 / 2^-12 relative through two layers and the deltas) 2^-7 / 2^-10."""
+    print(f"batch passes {prec} n={n}", flush=True)
+    prob = small_problem(d=5, width=128, n_hidden=3)
+    ctx = B.best_init(prob, n_chains=64, precision=prec, seed=1)
+    rng = np.random.default_rng(n)
+    x = prob["gauss_mean"] + 1.5 * rng.normal(size=(n, 5)) * np.sqrt(np.diag(prob["closed_cov"]))
+    w = rng.normal(size=n)
+    g = B.best_logL_param_grad(ctx, torch.tensor(x.T.copy(), device="cuda"),
+                               torch.tensor(w, device="cuda")).cpu().numpy()
+    ref, _ = OM.param_grad(prob["mlp_params"], OT.normalise(prob, x), prob["mlp_coef"] * w, 5,
+                           128, 3)
+    tol = {"fp32": 2e-5, "fp16": 2.0 ** -10, "bf16": 2.0 ** -7}[prec]
+    assert np.abs(g - ref).max() < tol * np.abs(ref).max()
