@@ -19,6 +19,7 @@ namespace best {
   hipError_t launch_step_##suf(int, const KArgs&, int, size_t, hipStream_t);                 \
   hipError_t launch_eval_##suf(int, const KArgs&, int, size_t, hipStream_t);                 \
   hipError_t launch_fit_##suf(const FitArgs&, hipStream_t);                                  \
+  hipError_t launch_adam_pack_##suf(const AdamArgs&, hipStream_t);                           \
   hipError_t launch_pack_##suf(const double*, int, int, int, void*, void*, void*, void*, void*, \
                                void*, hipStream_t);
 BEST_DECL_PREC(f64)
@@ -47,6 +48,14 @@ hipError_t launch_fit(int prec, const FitArgs& a, hipStream_t s) {
     case BEST_FP32: return launch_fit_f32(a, s);
     case BEST_FP16: return launch_fit_f16(a, s);
     case BEST_BF16: return launch_fit_bf16(a, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+hipError_t launch_adam_pack(int prec, const AdamArgs& a, hipStream_t s) {
+  switch (prec) {
+    case BEST_FP32: return launch_adam_pack_f32(a, s);
+    case BEST_FP16: return launch_adam_pack_f16(a, s);
+    case BEST_BF16: return launch_adam_pack_bf16(a, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1499,9 +1508,10 @@ static int trainer_buffers(best_trainer* t, int64_t B) {
   return BEST_OK;
 }
 
-// Forward + backward over one minibatch and the weight gradients into t->g.
+// Forward + backward over one minibatch: the weight gradients into t->g, the sums of squared
+// residuals of its column tiles into t->loss_part.
 static int trainer_grad(best_trainer* t, const float* t_in, const float* y, const int32_t* perm,
-                        int64_t batch0, int64_t B, double* loss_out_dev) {
+                        int64_t batch0, int64_t B) {
   FitArgs a{};
   a.mp = t->mp;
   a.round_h = t->mp.lds_h;
@@ -1513,7 +1523,6 @@ static int trainer_grad(best_trainer* t, const float* t_in, const float* y, cons
   t->bufs.fill(a, B);
   THIPCHK(t, launch_fit(t->prec, a, t->stream));
   THIPCHK(t, launch_dw(a, t->g, t->offs, t->stream));
-  THIPCHK(t, launch_sum(t->loss_part, (int)(B / 16), 1.0 / (double)B, loss_out_dev, t->stream));
   return BEST_OK;
 }
 
@@ -1604,7 +1613,8 @@ int best_train_grad(best_trainer* t, const float* t_in, const float* y, int64_t 
   if (!t_in || !y || batch < 16 || batch % 16) return tfail(t, BEST_EINVAL, "batch must be a positive multiple of 16");
   int rc = trainer_buffers(t, batch);
   if (rc) return rc;
-  if ((rc = trainer_grad(t, t_in, y, t->ident, 0, batch, t->loss_steps))) return rc;
+  if ((rc = trainer_grad(t, t_in, y, t->ident, 0, batch))) return rc;
+  THIPCHK(t, launch_sum(t->loss_part, (int)(batch / 16), 1.0 / (double)batch, t->loss_steps, t->stream));
   double l = 0;
   if (grad) THIPCHK(t, hipMemcpyAsync(grad, t->g, t->np * 8, hipMemcpyDeviceToHost, t->stream));
   THIPCHK(t, hipMemcpyAsync(&l, t->loss_steps, 8, hipMemcpyDeviceToHost, t->stream));
@@ -1626,14 +1636,15 @@ int best_train_epoch(best_trainer* t, const float* t_in, const float* y, int64_t
   if (rc) return rc;
   const double b1 = 0.9, b2 = 0.999, eps = 1e-8;
   for (int64_t i = 0; i < nb; ++i) {
-    if ((rc = trainer_grad(t, t_in, y, perm, i * batch, batch, t->loss_steps + i))) return rc;
+    if ((rc = trainer_grad(t, t_in, y, perm, i * batch, batch))) return rc;
     t->t += 1;
     const double c1 = 1.0 - std::pow(b1, (double)t->t), c2 = 1.0 - std::pow(b2, (double)t->t);
     const double s = (double)(step0 + i);
     const double lr = lr1 + 0.5 * (lr0 - lr1) * (1.0 + std::cos(M_PI * s / (double)total_steps));
-    THIPCHK(t, launch_adam(t->p, t->m, t->v, t->g, t->np, lr, b1, b2, eps, c1, c2, t->stream));
-    THIPCHK(t, launch_pack(t->prec, t->p, t->d, t->H, t->nh, t->wf, t->wb, t->w1f, t->w1t,
-                           t->bias, t->wout, t->stream));
+    const AdamArgs a{t->p, t->m, t->v, t->g, lr, b1, b2, eps, c1, c2, t->d, t->H, t->nh,
+                     t->wf, t->wb, t->w1f, t->w1t, t->bias, t->wout, t->loss_part,
+                     (int)(batch / 16), 1.0 / (double)batch, t->loss_steps + i};
+    THIPCHK(t, launch_adam_pack(t->prec, a, t->stream));
   }
   if (mean_loss) {
     std::vector<double> ls(nb);

@@ -19,6 +19,7 @@ hipError_t launch_eval(int prec, int MT, const KArgs& a, int grid, size_t lds, h
 hipError_t launch_pack(int prec, const double* flat, int d, int H, int nh, void* wf, void* wb,
                        void* w1f, void* w1t, void* bias, void* wout, hipStream_t s);
 hipError_t launch_fit(int prec, const FitArgs& a, hipStream_t s);
+hipError_t launch_adam_pack(int prec, const AdamArgs& a, hipStream_t s);
 
 // kernels_aux.hip
 hipError_t launch_init_positions(const Target& tg, const State& S, const Rng& rng, int mode,
@@ -50,8 +51,6 @@ struct InputScaling {  // kernel argument: per-component centre and inverse scal
 };
 hipError_t launch_normalise_inputs(const double* x, int64_t n, int d, const InputScaling& sc,
                                    float* t, hipStream_t s);
-hipError_t launch_adam(double* p, double* m, double* v, const double* g, int64_t n, double lr,
-                       double b1, double b2, double eps, double c1, double c2, hipStream_t s);
 hipError_t launch_dw(const FitArgs& a, double* grad, const int64_t* offs, hipStream_t s);
 hipError_t launch_sum(const double* part, int n, double scale, double* out, hipStream_t s);
 hipError_t launch_standardise(const double* y, int64_t n, float* out, double* scratch,

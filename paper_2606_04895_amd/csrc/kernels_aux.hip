@@ -381,22 +381,6 @@ __global__ void normalise_inputs_kernel(const double* x, int64_t n, int d, Input
   }
 }
 
-// ---- training: Adam on the FP64 master parameters --------------------------------------
-__global__ void adam_kernel(double* p, double* m, double* v, const double* g, int64_t n,
-                            double lr, double b1, double b2, double eps, double c1,
-                            double c2) {
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const double ge = g[e];
-    const double me = b1 * m[e] + (1.0 - b1) * ge;
-    const double ve = b2 * v[e] + (1.0 - b2) * ge * ge;
-    m[e] = me;
-    v[e] = ve;
-    const double mh = me / c1, vh = ve / c2;
-    p[e] = p[e] - lr * mh / (sqrt(vh) + eps);
-  }
-}
-
 // ---- weight gradients: one launch for every parameter ------------------------------------
 // Blocks [0, n_gemm): dW_l = delta_l h_{l-1}^T, l >= 2, on FP32 MFMA, K = batch; the blocks
 // after them: dW_1, the biases, w_out and b_out as FP64 sums over the batch.
@@ -712,13 +696,6 @@ hipError_t launch_normalise_inputs(const double* x, int64_t n, int d, const Inpu
                                    float* t, hipStream_t s) {
   hipLaunchKernelGGL(normalise_inputs_kernel, dim3(grid_for((int64_t)d * n)), dim3(kAuxThreads),
                      0, s, x, n, d, sc, t);
-  return hipGetLastError();
-}
-
-hipError_t launch_adam(double* p, double* m, double* v, const double* g, int64_t n, double lr,
-                       double b1, double b2, double eps, double c1, double c2, hipStream_t s) {
-  hipLaunchKernelGGL(adam_kernel, dim3(grid_for(n)), dim3(kAuxThreads), 0, s, p, m, v, g, n, lr,
-                     b1, b2, eps, c1, c2);
   return hipGetLastError();
 }
 
