@@ -188,7 +188,7 @@ struct best_ctx {
   int ad_blocks = 256;
   double *ev_x = nullptr, *ev_lp = nullptr, *ev_g = nullptr;
   int64_t ev_cap = 0;
-  double *es_mean = nullptr, *es_ssq = nullptr, *es_part = nullptr;
+  double *es_mean = nullptr, *es_ssq = nullptr, *es_part = nullptr, *es_out = nullptr;
   int64_t es_cap = 0;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   double* nu_buf = nullptr;  // NUTS trajectory buffers (allocated by the first NUTS call)
@@ -578,6 +578,7 @@ int best_init(best_ctx** out, const best_problem* p, const best_config* c) {
   if (h->mem.upload(&h->da, da, 9, h->stream) != hipSuccess ||
       h->mem.alloc(&h->st_i, 4) != hipSuccess || h->mem.alloc(&h->st_d, 4) != hipSuccess ||
       h->mem.alloc(&h->ad_info, 4) != hipSuccess ||
+      h->mem.alloc(&h->es_out, (size_t)d * (4 + kEssWin * kEssLB)) != hipSuccess ||
       h->mem.alloc(&h->ad_part, (size_t)h->ad_blocks * (kMaxD + kMaxD * (kMaxD + 1) / 2)) !=
           hipSuccess)
     return bail(fail(h, BEST_ENOMEM, "small buffers"));
@@ -1039,35 +1040,29 @@ int best_set_mlp(best_ctx* h, const double* params, double mlp_coef, double offs
 }  // extern "C"
 
 // Multi-chain ESS of a record with the given device scratch: mean and ssq [d][N], part
-// [d][ceil(N/64)][kEssLB] doubles.
+// d ceil(N/64) ess_segments() kEssWin kEssLB doubles, out d (4 + kEssWin kEssLB).  The first launch
+// covers kEssLB lags, which a converged record's Geyer sequence rarely outlives; the following ones
+// kEssWin windows each.
 static int ess_impl(best_ctx* h, const float* record, int64_t T, double* es_mean,
-                    double* es_ssq, double* es_part, double* ess_out, int32_t* flags_out) {
+                    double* es_ssq, double* es_part, double* es_out, double* ess_out,
+                    int32_t* flags_out) {
   const int d = h->d;
-  const int64_t N = h->N, nblk = (N + 63) / 64;
+  const int64_t N = h->N;
+  const int n_seg = ess_segments(T, d, N);
+  double* lag_dev = es_out + 4 * d;
   HIPCHK(h, launch_ess_chain_stats(record, T, d, N, es_mean, es_ssq, h->stream));
-  std::vector<double> mean((size_t)d * N), ssq((size_t)d * N), part((size_t)d * nblk * kEssLB);
-  HIPCHK(h, hipMemcpyAsync(mean.data(), es_mean, mean.size() * 8, hipMemcpyDeviceToHost, h->stream));
-  HIPCHK(h, hipMemcpyAsync(ssq.data(), es_ssq, ssq.size() * 8, hipMemcpyDeviceToHost, h->stream));
+  HIPCHK(h, launch_ess_param_stats(es_mean, es_ssq, N, d, es_out, h->stream));
+  HIPCHK(h, launch_ess_autocov(record, es_mean, T, d, N, 0, 1, n_seg, es_part, lag_dev, h->stream));
+  std::vector<double> got((size_t)d * (4 + kEssWin * kEssLB));
+  HIPCHK(h, hipMemcpyAsync(got.data(), es_out, (size_t)d * (4 + kEssLB) * 8, hipMemcpyDeviceToHost,
+                           h->stream));
   HIPCHK(h, hipStreamSynchronize(h->stream));
-  std::vector<double> W(d), var_plus(d);
+  std::vector<double> W(d), var_plus(d), scale(d);
   for (int i = 0; i < d; ++i) {
-    double w = 0, mm = 0;
-    for (int64_t c = 0; c < N; ++c) {
-      w += ssq[i * N + c] / (double)(T - 1);
-      mm += mean[i * N + c];
-    }
-    w /= (double)N;
-    mm /= (double)N;
-    double b = 0;
-    if (N > 1) {
-      for (int64_t c = 0; c < N; ++c) {
-        const double dm = mean[i * N + c] - mm;
-        b += dm * dm;
-      }
-      b /= (double)(N - 1);
-    }
-    W[i] = w;
-    var_plus[i] = (double)(T - 1) / (double)T * w + b;
+    W[i] = got[4 * i] / (double)(T - 1) / (double)N;
+    const double b = N > 1 ? got[4 * i + 2] / (double)(N - 1) : 0.0;
+    var_plus[i] = (double)(T - 1) / (double)T * W[i] + b;
+    scale[i] = got[4 * i + 3];
   }
   std::vector<std::vector<double>> rho(d);
   std::vector<int> done(d, 0), flag(d, BEST_ESS_OK);
@@ -1075,24 +1070,27 @@ static int ess_impl(best_ctx* h, const float* record, int64_t T, double* es_mean
   // every chain constant over the window: no autocorrelation estimate exists.  W = 0 up to
   // the rounding of the chain means: W <= (1e-10 max_m |mean_m|)^2
   for (int i = 0; i < d; ++i) {
-    double scale = 0;
-    for (int64_t c = 0; c < N; ++c) scale = std::max(scale, std::fabs(mean[i * N + c]));
-    if (!(W[i] > (1e-10 * scale) * (1e-10 * scale))) {
+    if (!(W[i] > (1e-10 * scale[i]) * (1e-10 * scale[i]))) {
       done[i] = 1;
       flag[i] = BEST_ESS_FROZEN;
     }
   }
   bool any_left = false;
   for (int i = 0; i < d; ++i) any_left |= !done[i];
-  for (int64_t lag0 = 0; any_left && lag0 < T; lag0 += kEssLB) {
-    HIPCHK(h, launch_ess_autocov(record, es_mean, T, d, N, lag0, es_part, h->stream));
-    HIPCHK(h, hipMemcpyAsync(part.data(), es_part, part.size() * 8, hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(h, hipStreamSynchronize(h->stream));
+  const double* lag_sum = got.data() + 4 * d;
+  int n_lag = kEssLB;
+  for (int64_t lag0 = 0; any_left && lag0 < T; lag0 += n_lag) {
+    if (lag0 > 0) {
+      n_lag = kEssWin * kEssLB;
+      HIPCHK(h, launch_ess_autocov(record, es_mean, T, d, N, lag0, kEssWin, n_seg, es_part, lag_dev,
+                                   h->stream));
+      HIPCHK(h, hipMemcpyAsync(got.data() + 4 * d, lag_dev, (size_t)d * n_lag * 8,
+                               hipMemcpyDeviceToHost, h->stream));
+      HIPCHK(h, hipStreamSynchronize(h->stream));
+    }
     for (int i = 0; i < d; ++i) {
-      for (int t = 0; t < kEssLB && lag0 + t < T; ++t) {
-        double g = 0;
-        for (int64_t b = 0; b < nblk; ++b) g += part[((size_t)i * nblk + b) * kEssLB + t];
-        const double gbar = g / ((double)N * (double)T);
+      for (int t = 0; t < n_lag && lag0 + t < T; ++t) {
+        const double gbar = lag_sum[(size_t)i * n_lag + t] / ((double)N * (double)T);
         rho[i].push_back(lag0 + t == 0 ? 1.0 : 1.0 - (W[i] - gbar) / var_plus[i]);
       }
     }
@@ -1143,18 +1141,19 @@ int best_ess(best_ctx* h, const float* record, int64_t T, double* ess_out, int32
   if (!record || !ess_out || T < 4) return fail(h, BEST_EINVAL, "record/ess_out NULL or T < 4");
   const int d = h->d;
   const int64_t N = h->N, nblk = (N + 63) / 64;
-  if (h->es_cap < N) {
+  const int64_t part = (int64_t)d * nblk * ess_segments(T, d, N) * kEssWin * kEssLB;
+  if (h->es_cap < part) {
     h->mem.release(h->es_mean);
     h->mem.release(h->es_ssq);
     h->mem.release(h->es_part);
     h->es_cap = 0;
     if (h->mem.alloc(&h->es_mean, (size_t)d * N) != hipSuccess ||
         h->mem.alloc(&h->es_ssq, (size_t)d * N) != hipSuccess ||
-        h->mem.alloc(&h->es_part, (size_t)d * nblk * kEssLB) != hipSuccess)
+        h->mem.alloc(&h->es_part, (size_t)part) != hipSuccess)
       return fail(h, BEST_ENOMEM, "ESS scratch");
-    h->es_cap = N;
+    h->es_cap = part;
   }
-  return ess_impl(h, record, T, h->es_mean, h->es_ssq, h->es_part, ess_out, flags_out);
+  return ess_impl(h, record, T, h->es_mean, h->es_ssq, h->es_part, h->es_out, ess_out, flags_out);
 }
 
 int best_ess_noalloc(best_ctx* h, const float* record, int64_t T, double* ess_out,
@@ -1171,12 +1170,13 @@ int best_ess_noalloc(best_ctx* h, const float* record, int64_t T, double* ess_ou
   int cur = -1;
   HIPCHK(h, hipGetDevice(&cur));
   if (cur != h->dev) return fail(h, BEST_ESTATE, "best_ess_noalloc: the context's device is not current");
-  // carve mean [d N], ssq [d N], part [d nblk kEssLB] out of the fixed array; the kernels
-  // write every element they later read, so nothing needs clearing between calls
+  // carve mean [d N], ssq [d N] and the partial sums (at most 2^21 doubles, see ess_segments) out
+  // of the fixed array; the kernels write every element they later read, so nothing needs
+  // clearing between calls
   double* mean = h->scratch;
   double* ssq = mean + dn;
   double* part = ssq + dn;
-  return ess_impl(h, record, T, mean, ssq, part, ess_out, flags_out);
+  return ess_impl(h, record, T, mean, ssq, part, h->es_out, ess_out, flags_out);
 }
 
 // ---------------------------------------------------------------------------------------

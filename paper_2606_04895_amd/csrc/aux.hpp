@@ -5,10 +5,21 @@
 
 namespace best {
 
-constexpr int kEssTS = 64;   // time-window rows per autocovariance pass
-constexpr int kEssLB = 128;  // lags per autocovariance pass
+constexpr int kEssLB = 32;   // lags per autocovariance window
+constexpr int kEssWin = 4;   // windows per launch after the first launch's single one
+// Time segments of the autocovariance launches: enough that 4096 waves (four per SIMD) share
+// the record, none shorter than 128 steps, and the partial sums of kEssWin windows no more than
+// 2^21 doubles where one segment fits in that (every size best_ess_noalloc takes).
+inline int ess_segments(int64_t T, int d, int64_t N) {
+  const int64_t rows = (int64_t)d * ((N + 63) / 64);
+  int64_t n = (4096 + rows - 1) / rows;
+  if (n > T / 128) n = T / 128;
+  const int64_t cap = ((int64_t)1 << 21) / (rows * kEssWin * kEssLB);
+  if (n > cap) n = cap;
+  return (int)(n < 1 ? 1 : n);
+}
 // Entry points that allocate nothing take their device scratch from one fixed array per
-// GPU (kernels_aux.hip).  The ESS passes need 4 d ceil(N/64) 64 doubles of it, so d times
+// GPU (kernels_aux.hip).  The ESS passes need up to 4 d ceil(N/64) 64 doubles of it, so d times
 // the 64-padded chain count is limited to kNoAllocMaxDN (32 MiB of scratch per GPU).
 constexpr int64_t kNoAllocMaxDN = (int64_t)1 << 20;
 constexpr int64_t kNoAllocScratchDoubles = 4 * kNoAllocMaxDN;
@@ -42,8 +53,11 @@ hipError_t launch_ess_chain_stats(const float* rec, int64_t T, int d, int64_t N,
 // doubles).  The first call for a device must have that device current; the address is
 // kept per device and later calls return it.
 hipError_t noalloc_scratch_address(int dev, double** p);
-hipError_t launch_ess_autocov(const float* rec, const double* mean, int64_t T, int d,
-                              int64_t N, int64_t lag0, double* part, hipStream_t s);
+hipError_t launch_ess_param_stats(const double* mean, const double* ssq, int64_t N, int d,
+                                  double* out, hipStream_t s);
+hipError_t launch_ess_autocov(const float* rec, const double* mean, int64_t T, int d, int64_t N,
+                              int64_t lag0, int n_win, int n_seg, double* part, double* out,
+                              hipStream_t s);
 hipError_t launch_transpose(const double* src, int64_t rows, int64_t cols, double* dst,
                             hipStream_t s);
 struct InputScaling {  // kernel argument: per-component centre and inverse scale

@@ -2,6 +2,7 @@
 // ensemble moments + jittered Cholesky (Sec. 3.2), multi-chain autocovariances for ESS,
 // Adam, and the training weight-gradient GEMMs.
 #include <mutex>
+#include <type_traits>
 
 #include "aux.hpp"
 
@@ -261,71 +262,182 @@ __global__ void moments_final_kernel(const double* part, int nblocks, int64_t co
   info[2] = ld;
 }
 
-// ---- ESS: per-chain mean and sum of squared deviations, thread per (param, chain) ------
-__global__ void ess_chain_stats_kernel(const float* rec, int64_t T, int d, int64_t N,
-                                       double* mean, double* ssq) {
-  const int64_t n = (int64_t)d * N;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int i = (int)(e / N);
-    const int64_t c = e % N;
-    double s = 0;
-    for (int64_t t = 0; t < T; ++t) s += rec[(t * d + i) * N + c];
-    const double m = s / (double)T;
-    double q = 0;
-    for (int64_t t = 0; t < T; ++t) {
-      const double y = rec[(t * d + i) * N + c] - m;
-      q += y * y;
+// ---- ESS ----------------------------------------------------------------------------------
+// Per-chain mean and sum of squared deviations: a workgroup holds 64 chains of one parameter, its
+// 16 waves every 16th step each, so a record of few chains still fills the chip.  One pass: the
+// sums are taken about the chain's first value x_0 (ssq = S2 - S1^2 / T; x_0 is one of the T values,
+// so S2 is at most T + 1 times ssq and the subtraction costs no more than T 2^-53).  Bound by the
+// record's bytes.  4000 x 6 x 4096 (393 MB): 97 us; a thread per chain with two passes took
+// 3190 us.
+constexpr int kStatWaves = 16;
+__global__ __launch_bounds__(64 * kStatWaves) void ess_chain_stats_kernel(const float* rec,
+                                                                          int64_t T, int d,
+                                                                          int64_t N, double* mean,
+                                                                          double* ssq) {
+  __shared__ double sh[2][kStatWaves][64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, i = blockIdx.y;
+  const int64_t c = (int64_t)blockIdx.x * 64 + lane;
+  const float* __restrict__ x = rec + (int64_t)i * N + (c < N ? c : N - 1);
+  const int64_t st = (int64_t)d * N;
+  const double x0 = x[0];
+  double s1 = 0, s2 = 0;
+#pragma unroll 8
+  for (int64_t t = wv; t < T; t += kStatWaves) {
+    const double u = (double)x[t * st] - x0;
+    s1 += u;
+    s2 += u * u;
+  }
+  sh[0][wv][lane] = s1;
+  sh[1][wv][lane] = s2;
+  __syncthreads();
+  if (wv == 0 && c < N) {
+    s1 = s2 = 0;
+    for (int w = 0; w < kStatWaves; ++w) {
+      s1 += sh[0][w][lane];
+      s2 += sh[1][w][lane];
     }
-    mean[e] = m;
-    ssq[e] = q;
+    mean[i * N + c] = x0 + s1 / (double)T;
+    const double q = s2 - s1 * s1 / (double)T;
+    ssq[i * N + c] = q < 0.0 ? 0.0 : q;  // NaN passes
   }
 }
 
-// Sum over the 64 chains of a block of sum_s y_s y_{s+t} for t in [lag0, lag0 + kEssLB).
-// grid = (ceil(N/64), d); LDS holds the two time windows of the block's chains.
-__global__ __launch_bounds__(kAuxThreads) void ess_autocov_kernel(const float* rec,
-                                                               const double* mean, int64_t T,
-                                                               int d, int64_t N, int64_t lag0,
-                                                               double* part) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  double* ya = (double*)smem;                      // [kEssTS][64]
-  double* yb = ya + kEssTS * 64;                   // [kEssTS + kEssLB][64]
-  const int cm = threadIdx.x & 63, lq = threadIdx.x >> 6;
-  const int i = blockIdx.y;
-  const int64_t c = (int64_t)blockIdx.x * 64 + cm;
-  const bool valid = c < N;
-  const double mc = valid ? mean[i * N + c] : 0.0;
-  double acc[kEssLB / 4];
-#pragma unroll
-  for (int k = 0; k < kEssLB / 4; ++k) acc[k] = 0;
-  for (int64_t s0 = 0; s0 < T; s0 += kEssTS) {
-    for (int r = lq; r < kEssTS; r += 4) {
-      const int64_t s = s0 + r;
-      ya[r * 64 + cm] = (valid && s < T) ? (double)rec[(s * d + i) * N + c] - mc : 0.0;
-    }
-    for (int r = lq; r < kEssTS + kEssLB; r += 4) {
-      const int64_t s = s0 + lag0 + r;
-      yb[r * 64 + cm] = (valid && s < T) ? (double)rec[(s * d + i) * N + c] - mc : 0.0;
-    }
-    __syncthreads();
+// Over the chains of one parameter: out = [sum ssq, mean of the means, sum (mean - that)^2,
+// max |mean|] (one workgroup per parameter, fixed order).
+__global__ void ess_param_stats_kernel(const double* mean, const double* ssq, int64_t N,
+                                       double* out) {
+  __shared__ double sh[kAuxThreads];
+  const double* m = mean + (int64_t)blockIdx.x * N;
+  const double* q = ssq + (int64_t)blockIdx.x * N;
+  double w = 0, s = 0, mx = 0;
 #pragma unroll 4
-    for (int r = 0; r < kEssTS; ++r) {
-      const double y0 = ya[r * 64 + cm];
-#pragma unroll
-      for (int k = 0; k < kEssLB / 4; ++k) acc[k] += y0 * yb[(r + lq + 4 * k) * 64 + cm];
-    }
-    __syncthreads();
+  for (int64_t c = threadIdx.x; c < N; c += kAuxThreads) {
+    w += q[c];
+    s += m[c];
+    mx = fmax(mx, fabs(m[c]));
   }
-  // reduce over the 64 chains in a fixed order
-  double* red = (double*)smem;  // [kEssLB][64]
-#pragma unroll
-  for (int k = 0; k < kEssLB / 4; ++k) red[(lq + 4 * k) * 64 + cm] = acc[k];
+  w = block_sum(w, sh);
+  const double mm = block_sum(s, sh) / (double)N;
+  double b = 0;
+#pragma unroll 4
+  for (int64_t c = threadIdx.x; c < N; c += kAuxThreads) {
+    const double dm = m[c] - mm;
+    b += dm * dm;
+  }
+  b = block_sum(b, sh);
+  sh[threadIdx.x] = mx;
   __syncthreads();
-  if (threadIdx.x < kEssLB) {
-    double s = 0;
-    for (int j = 0; j < 64; ++j) s += red[threadIdx.x * 64 + j];
-    part[((int64_t)i * gridDim.x + blockIdx.x) * kEssLB + threadIdx.x] = s;
+  if (threadIdx.x == 0) {
+    for (int t = 1; t < kAuxThreads; ++t) mx = fmax(mx, sh[t]);
+    double* o = out + 4 * blockIdx.x;
+    o[0] = w;
+    o[1] = mm;
+    o[2] = b;
+    o[3] = mx;
+  }
+}
+
+// Sums over chains and steps of y_s y_{s - lag} (y = x - chain mean, zero outside the record) for
+// windows of kEssLB lags (LAG0: the window of lags 0 ..).  One wave holds 64 chains of one parameter over one of S time segments:
+// a lane keeps its chain's last kEssLB (delayed) values and the kEssLB sums in registers, so a step
+// is one load and kEssLB FP64 FMAs without LDS.  Bound by the FP64 rate (and by the record's bytes
+// for the first window): 4000 x 6 x 4096, 32 lags 150 us, of which 86 us are the FMAs.  The
+// time segments give small ensembles enough waves; with the windows staged through LDS (an LDS
+// read per FMA, 128 lags) the first pass took 9100 us.
+constexpr int kEssChunk = 16;  // steps loaded together (kEssLB a multiple)
+template <bool LAG0>
+__global__ __launch_bounds__(64, LAG0 ? 3 : 2) void ess_autocov_kernel(const float* rec, const double* mean,
+                                                            int64_t T, int d, int64_t N,
+                                                            int64_t lag0, int n_win, int64_t seg,
+                                                            double* part) {
+  const int lane = threadIdx.x, i = blockIdx.y, win = blockIdx.z % n_win, sg = blockIdx.z / n_win;
+  const int n_seg = gridDim.z / n_win;
+  const int64_t cb = blockIdx.x, st = (int64_t)d * N;
+  const bool valid = cb * 64 + lane < N;
+  const unsigned cl = (unsigned)(valid ? lane : N - 1 - cb * 64);  // idle lanes repeat a chain
+  const int64_t lag = LAG0 ? 0 : lag0 + (int64_t)win * kEssLB;
+  const float* __restrict__ x = rec + (int64_t)i * N + cb * 64;
+  const double mc = mean[(int64_t)i * N + cb * 64 + cl];
+  const int64_t s0 = sg * seg, s1 = min(T, s0 + seg);
+  double acc[kEssLB], w[kEssLB];
+#pragma unroll
+  for (int k = 0; k < kEssLB; ++k) acc[k] = 0;
+  // steps [s, s + kEssChunk), window slots J ..; zeros for the steps past the segment and for
+  // partners before the record (loads at clamped steps, the conditions are scalar)
+  auto chunk = [&](int64_t s, auto Jc) {
+    constexpr int J = decltype(Jc)::value;
+    float a[kEssChunk], b[kEssChunk];
+    const float* p = x + (s < T ? s : T - 1) * st;
+    const float* q = x + (s > lag ? s - lag : 0) * st;
+#pragma unroll
+    for (int j = 0; j < kEssChunk; ++j) {
+      a[j] = p[cl];
+      if (s + j + 1 < T) p += st;
+      if constexpr (!LAG0) {
+        b[j] = q[cl];
+        if (s + j >= lag) q += st;  // s + j < T or unused, so q stays in the record
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < kEssChunk; ++j) {
+      double y = (double)a[j] - mc;
+      if (s + j >= s1) y = 0.0;
+      // w[slot] holds the delayed value of the latest step congruent to slot; at lag 0 that is
+      // y itself (zero past the segment, where it only meets zeros)
+      if constexpr (LAG0) w[J + j] = y;
+      else w[J + j] = s + j >= lag ? (double)b[j] - mc : 0.0;
+#pragma unroll
+      for (int k = 0; k < kEssLB; ++k) acc[k] += y * w[(J + j - k + kEssLB) % kEssLB];
+      __builtin_amdgcn_sched_barrier(0);  // keep the conversions from piling up in registers
+    }
+  };
+  if (s0 < s1 && s1 > lag) {
+    const int64_t u0 = s0 - kEssLB - lag;
+    const float* q = x + (u0 > 0 ? u0 : 0) * st;
+#pragma unroll
+    for (int j = 0; j < kEssLB; ++j) {
+      w[j] = u0 + j >= 0 ? (double)q[cl] - mc : 0.0;
+      if (u0 + j >= 0) q += st;
+    }
+    for (int64_t s = s0; s < s1; s += kEssLB) {
+      chunk(s, std::integral_constant<int, 0>{});
+      chunk(s + kEssChunk, std::integral_constant<int, kEssChunk>{});
+    }
+  }
+  // sum over the 64 chains: halve the sums per lane while pairing lanes
+#pragma unroll
+  for (int k = 0; k < kEssLB; ++k) acc[k] = valid ? acc[k] : 0.0;
+#pragma unroll
+  for (int n = kEssLB / 2, o = 32; n >= 1; n >>= 1, o >>= 1) {
+    const bool up = lane & o;
+#pragma unroll
+    for (int k = 0; k < kEssLB / 2; ++k) {
+      if (k < n) {
+        const double send = up ? acc[k] : acc[k + n], keep = up ? acc[k + n] : acc[k];
+        acc[k] = keep + __shfl_xor(send, o, 64);
+      }
+    }
+  }
+  const double r = acc[0] + __shfl_xor(acc[0], 1, 64);
+  if (!(lane & 1))
+    part[(((int64_t)i * gridDim.x + cb) * n_seg + sg) * (n_win * kEssLB) + win * kEssLB + (lane >> 1)] = r;
+}
+
+// out[i][l] = sum over the n partial sums of parameter i, eight interleaved runs in order
+__global__ void ess_sum_kernel(const double* part, int64_t n, int n_lag, double* out) {
+  __shared__ double sh[8][kEssLB];
+  const int i = blockIdx.x, l = threadIdx.x % kEssLB, q = threadIdx.x / kEssLB;
+  const int lag = blockIdx.y * kEssLB + l;
+  const double* p = part + (int64_t)i * n * n_lag + lag;
+  double s = 0;
+#pragma unroll 4
+  for (int64_t b = q; b < n; b += 8) s += p[b * n_lag];
+  sh[q][l] = s;
+  __syncthreads();
+  if (q == 0) {
+    s = 0;
+    for (int w = 0; w < 8; ++w) s += sh[w][l];
+    out[i * n_lag + lag] = s;
   }
 }
 
@@ -669,19 +781,34 @@ hipError_t launch_moment_sums(const float* rec, const double* xs, int64_t T, int
 
 hipError_t launch_ess_chain_stats(const float* rec, int64_t T, int d, int64_t N, double* mean,
                                   double* ssq, hipStream_t s) {
-  hipLaunchKernelGGL(ess_chain_stats_kernel, dim3(grid_for((int64_t)d * N)), dim3(kAuxThreads),
-                     0, s, rec, T, d, N, mean, ssq);
+  hipLaunchKernelGGL(ess_chain_stats_kernel, dim3((unsigned)((N + 63) / 64), (unsigned)d),
+                     dim3(64 * kStatWaves), 0, s, rec, T, d, N, mean, ssq);
   return hipGetLastError();
 }
 
-hipError_t launch_ess_autocov(const float* rec, const double* mean, int64_t T, int d,
-                              int64_t N, int64_t lag0, double* part, hipStream_t s) {
-  const size_t lds = (size_t)(2 * kEssTS + kEssLB) * 64 * sizeof(double);
-  hipError_t e = hipFuncSetAttribute((const void*)ess_autocov_kernel,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+hipError_t launch_ess_param_stats(const double* mean, const double* ssq, int64_t N, int d,
+                                  double* out, hipStream_t s) {
+  hipLaunchKernelGGL(ess_param_stats_kernel, dim3((unsigned)d), dim3(kAuxThreads), 0, s, mean, ssq,
+                     N, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_ess_autocov(const float* rec, const double* mean, int64_t T, int d, int64_t N,
+                              int64_t lag0, int n_win, int n_seg, double* part, double* out,
+                              hipStream_t s) {
+  const int64_t nblk = (N + 63) / 64;
+  const int64_t seg = ((T + n_seg - 1) / n_seg + kEssLB - 1) / kEssLB * kEssLB;
+  const dim3 grid((unsigned)nblk, (unsigned)d, (unsigned)(n_seg * n_win));
+  if (lag0 == 0)
+    hipLaunchKernelGGL((ess_autocov_kernel<true>), grid, dim3(64), 0, s, rec, mean, T, d, N, lag0,
+                       1, seg, part);
+  else
+    hipLaunchKernelGGL((ess_autocov_kernel<false>), grid, dim3(64), 0, s, rec, mean, T, d, N, lag0,
+                       n_win, seg, part);
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(ess_autocov_kernel, dim3((unsigned)((N + 63) / 64), (unsigned)d),
-                     dim3(kAuxThreads), lds, s, rec, mean, T, d, N, lag0, part);
+  hipLaunchKernelGGL(ess_sum_kernel, dim3((unsigned)d, (unsigned)n_win), dim3(8 * kEssLB), 0, s, part,
+                     nblk * n_seg, n_win * kEssLB, out);
   return hipGetLastError();
 }
 
