@@ -301,8 +301,9 @@ int best_ess_noalloc(best_ctx *h, const float *record, int64_t T, double *ess_ou
 
 /* ---- convergence metrics (Sec. 4.1) ----
  * Samples are device records [T][d][n_chains] (floats, chain fastest), as best_step writes
- * them; d is the context's.  Results are host scalars / arrays; each call allocates its
- * device scratch, synchronises the stream and frees it. */
+ * them; d is the context's.  Results are host scalars / arrays; each call synchronises the
+ * stream.  The device scratch is one buffer per context, grown to the largest call and kept up
+ * to 512 MiB (a larger one is freed at the end of its call; BEST_ENOMEM if it cannot grow). */
 
 /* Gelman-Rubin type statistic of Sec. 4.1: B = covariance of the chain means (unbiased),
  * W = mean of the chain covariances (unbiased); with D = diag(sqrt(B_ii)),

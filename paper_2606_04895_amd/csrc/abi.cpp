@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <string>
 #include <vector>
 
@@ -190,6 +191,8 @@ struct best_ctx {
   int64_t ev_cap = 0;
   double *es_mean = nullptr, *es_ssq = nullptr, *es_part = nullptr, *es_out = nullptr;
   int64_t es_cap = 0;
+  char* met = nullptr;  // scratch of the metric calls (see MetricScratch)
+  size_t met_cap = 0;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   double* nu_buf = nullptr;  // NUTS trajectory buffers (allocated by the first NUTS call)
   double* mult = nullptr;    // per-dimension step multipliers [d] (MALA, MH)
@@ -1186,14 +1189,40 @@ int best_ess_noalloc(best_ctx* h, const float* record, int64_t T, double* ess_ou
 
 namespace {
 
-struct DevBuf {  // temporary device buffer of one metric call
-  void* p = nullptr;
-  ~DevBuf() {
-    if (p) (void)hipFree(p);
+// Device scratch of one metric call, carved from the context's metric buffer.  The buffer grows to
+// the largest call (growing frees the old one, which waits for the device) and is kept up to
+// kMetricKeep bytes: an allocation and release of a few hundred MB costs as much as the
+// kernels that use it (226 MB: 0.25 ms).  Larger ones are released at the end of the call.
+constexpr size_t kMetricKeep = (size_t)512 << 20;
+struct MetricScratch {
+  best_ctx* h;
+  size_t used = 0;
+  explicit MetricScratch(best_ctx* c) : h(c) {}
+  ~MetricScratch() {
+    if (h->met_cap > kMetricKeep) {
+      h->mem.release(h->met);
+      h->met = nullptr;
+      h->met_cap = 0;
+    }
   }
-  hipError_t alloc(size_t bytes) { return hipMalloc(&p, bytes ? bytes : 16); }
-  double* f64() const { return (double*)p; }
-  int* i32() const { return (int*)p; }
+  static size_t round(size_t b) { return (b + 255) / 256 * 256; }
+  bool reserve(std::initializer_list<size_t> parts) {
+    size_t need = 0;
+    for (size_t b : parts) need += round(b);
+    if (need <= h->met_cap) return true;
+    h->mem.release(h->met);
+    h->met = nullptr;
+    h->met_cap = 0;
+    if (h->mem.alloc(&h->met, need) != hipSuccess) return false;
+    h->met_cap = need;
+    return true;
+  }
+  template <class T>
+  T* take(size_t bytes) {  // in the order and sizes of reserve()
+    T* p = (T*)(h->met + used);
+    used += round(bytes);
+    return p;
+  }
 };
 
 // Eigenvalues of a symmetric d x d matrix (row-major, overwritten) by cyclic Jacobi rotations
@@ -1246,18 +1275,26 @@ std::vector<double> scatter_matrix(const std::vector<double>& sums, int d, doubl
   return S;
 }
 
-int upload_whitening(best_ctx* h, const double* mu, const double* L, DevBuf& mu_d,
-                     DevBuf& L_d) {
+int check_whitening(best_ctx* h, const double* mu, const double* L) {
   if (!mu) return BEST_OK;
   const int d = h->d;
   if (!L) return fail(h, BEST_EINVAL, "whitening needs both mu and L");
   for (int i = 0; i < d; ++i)
     if (!(L[i * d + i] > 0) || !std::isfinite(L[i * d + i]))
       return fail(h, BEST_EINVAL, "L must have a positive diagonal");
-  HIPCHK(h, mu_d.alloc((size_t)d * 8));
-  HIPCHK(h, L_d.alloc((size_t)d * d * 8));
-  HIPCHK(h, hipMemcpyAsync(mu_d.p, mu, (size_t)d * 8, hipMemcpyHostToDevice, h->stream));
-  HIPCHK(h, hipMemcpyAsync(L_d.p, L, (size_t)d * d * 8, hipMemcpyHostToDevice, h->stream));
+  return BEST_OK;
+}
+
+// (mu, L) as one device array of d + d^2 doubles; null pointers stay null.
+int upload_whitening(best_ctx* h, const double* mu, const double* L, double* dev,
+                     const double** mu_d, const double** L_d) {
+  *mu_d = *L_d = nullptr;
+  if (!mu) return BEST_OK;
+  const size_t d = h->d;
+  HIPCHK(h, hipMemcpyAsync(dev, mu, d * 8, hipMemcpyHostToDevice, h->stream));
+  HIPCHK(h, hipMemcpyAsync(dev + d, L, d * d * 8, hipMemcpyHostToDevice, h->stream));
+  *mu_d = dev;
+  *L_d = dev + d;
   return BEST_OK;
 }
 
@@ -1271,26 +1308,29 @@ int best_rhat(best_ctx* h, const float* samples, int64_t T, int64_t n_chains, do
     return fail(h, BEST_EINVAL, "samples/rminus1 NULL, T < 2 or n_chains < 2");
   const int d = h->d, np = d + d * (d + 1) / 2, nblocks = 256;
   const int64_t N = n_chains;
-  DevBuf mean, ssq, part, sums, shift0;
-  HIPCHK(h, mean.alloc((size_t)d * N * 8));
-  HIPCHK(h, ssq.alloc((size_t)d * N * 8));
-  HIPCHK(h, part.alloc((size_t)nblocks * np * 8));
-  HIPCHK(h, sums.alloc((size_t)np * 8));
-  HIPCHK(h, shift0.alloc((size_t)d * 8));
+  const size_t bc = (size_t)d * N * 8, bp = (size_t)nblocks * np * 8;
+  MetricScratch ms(h);
+  if (!ms.reserve({bc, bc, bp, (size_t)np * 8, (size_t)d * 8}))
+    return fail(h, BEST_ENOMEM, "metric scratch");
+  double* mean = ms.take<double>(bc);
+  double* ssq = ms.take<double>(bc);
+  double* part = ms.take<double>(bp);
+  double* sums = ms.take<double>((size_t)np * 8);
+  double* shift0 = ms.take<double>((size_t)d * 8);
   std::vector<double> sw(np), sb(np);
   // chain means, then the within-chain scatter about each chain's own mean
-  HIPCHK(h, launch_ess_chain_stats(samples, T, d, N, mean.f64(), ssq.f64(), h->stream));
-  HIPCHK(h, launch_moment_sums(samples, nullptr, T, N, N, d, mean.f64(), N,
-                               part.f64(), nblocks, h->stream));
-  HIPCHK(h, launch_sum_parts(part.f64(), nblocks, np, sums.f64(), h->stream));
-  HIPCHK(h, hipMemcpyAsync(sw.data(), sums.p, (size_t)np * 8, hipMemcpyDeviceToHost, h->stream));
+  HIPCHK(h, launch_ess_chain_stats(samples, T, d, N, mean, ssq, h->stream));
+  HIPCHK(h, launch_moment_sums(samples, nullptr, T, N, N, d, mean, N,
+                               part, nblocks, h->stream));
+  HIPCHK(h, launch_sum_parts(part, nblocks, np, sums, h->stream));
+  HIPCHK(h, hipMemcpyAsync(sw.data(), sums, (size_t)np * 8, hipMemcpyDeviceToHost, h->stream));
   // scatter of the chain means about chain 0's mean
-  HIPCHK(h, hipMemcpy2DAsync(shift0.p, 8, mean.p, (size_t)N * 8, 8, d, hipMemcpyDeviceToDevice,
+  HIPCHK(h, hipMemcpy2DAsync(shift0, 8, mean, (size_t)N * 8, 8, d, hipMemcpyDeviceToDevice,
                              h->stream));
-  HIPCHK(h, launch_moment_sums(nullptr, mean.f64(), 1, N, N, d, shift0.f64(), 0,
-                               part.f64(), nblocks, h->stream));
-  HIPCHK(h, launch_sum_parts(part.f64(), nblocks, np, sums.f64(), h->stream));
-  HIPCHK(h, hipMemcpyAsync(sb.data(), sums.p, (size_t)np * 8, hipMemcpyDeviceToHost, h->stream));
+  HIPCHK(h, launch_moment_sums(nullptr, mean, 1, N, N, d, shift0, 0,
+                               part, nblocks, h->stream));
+  HIPCHK(h, launch_sum_parts(part, nblocks, np, sums, h->stream));
+  HIPCHK(h, hipMemcpyAsync(sb.data(), sums, (size_t)np * 8, hipMemcpyDeviceToHost, h->stream));
   HIPCHK(h, hipStreamSynchronize(h->stream));
   // W = mean of the chain covariances, B = covariance of the chain means (both unbiased)
   std::vector<double> W = scatter_matrix(sw, d, (double)(T * N), (double)N * (double)(T - 1), false);
@@ -1355,32 +1395,26 @@ int best_credible(best_ctx* h, const float* samples, int64_t T, int64_t n_chains
   const int64_t n = T * n_chains;
   if (n >= ((int64_t)1 << 31)) return fail(h, BEST_EINVAL, "more than 2^31 - 1 draws");
   int rc;
-  DevBuf mu_d, L_d, z, sorted, temp;
-  if ((rc = upload_whitening(h, mu, L, mu_d, L_d))) return rc;
-  HIPCHK(h, z.alloc((size_t)d * n * 8));
-  HIPCHK(h, sorted.alloc((size_t)n * 8));
-  HIPCHK(h, launch_whiten_points(samples, T, d, n_chains, mu_d.f64(), L_d.f64(),
-                                 z.f64(), n, h->stream));
-  size_t tb = 0;
-  HIPCHK(h, sort_keys_f64(nullptr, &tb, nullptr, nullptr, n, h->stream));
-  HIPCHK(h, temp.alloc(tb));
+  if ((rc = check_whitening(h, mu, L))) return rc;
+  const size_t bw = (size_t)d * (d + 1) * 8, bz = (size_t)d * n * 8, bs = select_scratch_bytes(d);
+  MetricScratch ms(h);
+  if (!ms.reserve({bw, bz, bs})) return fail(h, BEST_ENOMEM, "metric scratch");
+  double* wh = ms.take<double>(bw);
+  double* z = ms.take<double>(bz);
+  void* sel = ms.take<char>(bs);
+  const double *mu_d, *L_d;
+  if ((rc = upload_whitening(h, mu, L, wh, &mu_d, &L_d))) return rc;
+  HIPCHK(h, launch_whiten_points(samples, T, d, n_chains, mu_d, L_d, z, n, h->stream));
   const double a = (1.0 - alpha) / 2.0;
   const double lev[2] = {a, 1.0 - a};
   std::vector<double> got((size_t)d * 4, 0.0);
-  std::vector<int64_t> kk(2);
-  for (int l = 0; l < 2; ++l) kk[l] = (int64_t)std::floor((double)(n - 1) * lev[l]);
-  for (int i = 0; i < d; ++i) {
-    size_t tbi = tb;
-    HIPCHK(h, sort_keys_f64(temp.p, &tbi, z.f64() + (size_t)i * n, sorted.f64(), n,
-                            h->stream));
-    for (int l = 0; l < 2; ++l) {
-      const int64_t k = std::min<int64_t>(kk[l], n - 1);
-      const int cnt = k + 1 < n ? 2 : 1;
-      HIPCHK(h, hipMemcpyAsync(&got[(size_t)i * 4 + 2 * l], sorted.f64() + k, cnt * 8,
-                               hipMemcpyDeviceToHost, h->stream));
-    }
+  int64_t ranks[4];
+  for (int l = 0; l < 2; ++l) {
+    const int64_t k = std::min<int64_t>((int64_t)std::floor((double)(n - 1) * lev[l]), n - 1);
+    ranks[2 * l] = k;
+    ranks[2 * l + 1] = std::min<int64_t>(k + 1, n - 1);
   }
-  HIPCHK(h, hipStreamSynchronize(h->stream));
+  HIPCHK(h, select_ranks(z, d, n, ranks, sel, got.data(), h->stream));
   double worst = 0;
   for (int i = 0; i < d; ++i) {
     double q[2];
@@ -1411,44 +1445,35 @@ int best_sliced_wasserstein(best_ctx* h, const float* a, int64_t Ta, int64_t cha
   const int d = h->d;
   const int64_t na = Ta * chains_a, nb = Tb * chains_b, n = na + nb;
   if (n >= ((int64_t)1 << 31)) return fail(h, BEST_EINVAL, "more than 2^31 - 1 draws");
-  const int P = std::min<int>(16, n_proj), nparts = 256;
+  // projections per batch: two key buffers of up to 2^23 keys, which the last-level cache holds
+  // between the passes of a batch
+  const int P = (int)std::max<int64_t>(1, std::min<int64_t>(n_proj, ((int64_t)1 << 23) / n));
   int rc;
-  DevBuf mu_d, L_d, za, zb, w, keys, ks, lab, ls, scan, part, res, temp;
-  if ((rc = upload_whitening(h, mu, L, mu_d, L_d))) return rc;
-  HIPCHK(h, za.alloc((size_t)d * na * 8));
-  HIPCHK(h, zb.alloc((size_t)d * nb * 8));
-  HIPCHK(h, w.alloc((size_t)n_proj * d * 8));
-  HIPCHK(h, keys.alloc((size_t)P * n * 8));
-  HIPCHK(h, ks.alloc((size_t)n * 8));
-  HIPCHK(h, lab.alloc((size_t)n * 4));
-  HIPCHK(h, ls.alloc((size_t)n * 4));
-  HIPCHK(h, scan.alloc((size_t)n * 4));
-  HIPCHK(h, part.alloc((size_t)nparts * 8));
-  HIPCHK(h, res.alloc((size_t)n_proj * 8));
-  size_t tb = 0;
-  HIPCHK(h, sliced_w1_workspace(n, &tb));
-  HIPCHK(h, temp.alloc(tb));
-  HIPCHK(h, launch_whiten_points(a, Ta, d, chains_a, mu_d.f64(), L_d.f64(),
-                                 za.f64(), na, h->stream));
-  HIPCHK(h, launch_whiten_points(b, Tb, d, chains_b, mu_d.f64(), L_d.f64(),
-                                 zb.f64(), nb, h->stream));
+  if ((rc = check_whitening(h, mu, L))) return rc;
+  const size_t bw = (size_t)d * (d + 1) * 8, ba = (size_t)d * na * 8, bb = (size_t)d * nb * 8,
+               bd = (size_t)n_proj * d * 8, bk = (size_t)P * n * 8,
+               bp = (size_t)P * sliced_w1_parts(n) * 8, br = (size_t)n_proj * 8;
+  MetricScratch ms(h);
+  if (!ms.reserve({bw, ba, bb, bd, bk, bk, bp, br})) return fail(h, BEST_ENOMEM, "metric scratch");
+  double* wh = ms.take<double>(bw);
+  double* za = ms.take<double>(ba);
+  double* zb = ms.take<double>(bb);
+  double* w = ms.take<double>(bd);
+  uint64_t* keys = ms.take<uint64_t>(bk);
+  uint64_t* tmp = ms.take<uint64_t>(bk);
+  double* part = ms.take<double>(bp);
+  double* res = ms.take<double>(br);
+  const double *mu_d, *L_d;
+  if ((rc = upload_whitening(h, mu, L, wh, &mu_d, &L_d))) return rc;
+  HIPCHK(h, launch_whiten_points(a, Ta, d, chains_a, mu_d, L_d, za, na, h->stream));
+  HIPCHK(h, launch_whiten_points(b, Tb, d, chains_b, mu_d, L_d, zb, nb, h->stream));
   const Rng rng{(uint32_t)(proj_seed & 0xFFFFFFFFu), (uint32_t)(proj_seed >> 32)};
-  HIPCHK(h, launch_directions(rng, d, n_proj, w.f64(), h->stream));
-  HIPCHK(h, hipMemsetD32Async((hipDeviceptr_t)lab.i32(), 0, (size_t)na, h->stream));
-  HIPCHK(h, hipMemsetD32Async((hipDeviceptr_t)(lab.i32() + na), 1, (size_t)nb, h->stream));
-  for (int k0 = 0; k0 < n_proj; k0 += P) {
-    const int pk = std::min(P, n_proj - k0);
-    const double* wk = w.f64() + (size_t)k0 * d;
-    HIPCHK(h, launch_project(za.f64(), d, na, na, wk, pk, keys.f64(), n, h->stream));
-    HIPCHK(h, launch_project(zb.f64(), d, nb, nb, wk, pk, keys.f64() + na, n,
-                             h->stream));
-    for (int p = 0; p < pk; ++p)
-      HIPCHK(h, sliced_w1_one(temp.p, tb, keys.f64() + (size_t)p * n, ks.f64(),
-                              lab.i32(), ls.i32(), scan.i32(), n, na, nb,
-                              part.f64(), nparts, res.f64() + k0 + p, h->stream));
-  }
+  HIPCHK(h, launch_directions(rng, d, n_proj, w, h->stream));
+  for (int k0 = 0; k0 < n_proj; k0 += P)
+    HIPCHK(h, launch_sliced_w1(za, na, zb, nb, d, w + (size_t)k0 * d, std::min(P, n_proj - k0), keys,
+                               tmp, part, res + k0, h->stream));
   std::vector<double> r(n_proj);
-  HIPCHK(h, hipMemcpyAsync(r.data(), res.p, (size_t)n_proj * 8, hipMemcpyDeviceToHost, h->stream));
+  HIPCHK(h, hipMemcpyAsync(r.data(), res, (size_t)n_proj * 8, hipMemcpyDeviceToHost, h->stream));
   HIPCHK(h, hipStreamSynchronize(h->stream));
   double s = 0;
   for (double v : r) s += v;

@@ -76,14 +76,16 @@ hipError_t launch_importance_weights(const double* lp, const double* le, int64_t
 hipError_t launch_whiten_points(const float* rec, int64_t T, int d, int64_t N, const double* mu,
                                 const double* L, double* z, int64_t zpitch, hipStream_t s);
 hipError_t launch_sum_parts(const double* part, int nblocks, int np, double* out, hipStream_t s);
-hipError_t sort_keys_f64(void* temp, size_t* temp_bytes, const double* in, double* out,
-                         int64_t n, hipStream_t s);
 hipError_t launch_directions(const Rng& rng, int d, int K, double* w, hipStream_t s);
-hipError_t launch_project(const double* z, int d, int64_t n, int64_t zpitch, const double* w,
-                          int P, double* keys, int64_t kpitch, hipStream_t s);
-hipError_t sliced_w1_workspace(int64_t n, size_t* temp_bytes);
-hipError_t sliced_w1_one(void* temp, size_t temp_bytes, const double* keys, double* keys_sorted,
-                         const int* labels, int* labels_sorted, int* scan, int64_t n, int64_t na,
-                         int64_t nb, double* part, int nparts, double* out, hipStream_t s);
+// W1 of P projections (w [P][d]) of the points za ([d][na]) and zb ([d][nb]) into out[P]; keys and
+// tmp: P (na + nb) words, part: P sliced_w1_parts(na + nb) doubles.
+int64_t sliced_w1_parts(int64_t n);
+hipError_t launch_sliced_w1(const double* za, int64_t na, const double* zb, int64_t nb, int d,
+                            const double* w, int P, uint64_t* keys, uint64_t* tmp, double* part,
+                            double* out, hipStream_t s);
+// Four order statistics of every row of z [d][n] (synchronises).
+size_t select_scratch_bytes(int d);
+hipError_t select_ranks(const double* z, int d, int64_t n, const int64_t* ranks, void* scratch,
+                        double* out, hipStream_t s);
 
 }  // namespace best

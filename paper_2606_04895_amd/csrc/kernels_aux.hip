@@ -129,12 +129,15 @@ __global__ void aies_record_kernel(State S, int d, float* rec, int64_t slot, int
 }
 
 // ---- ensemble moments, pass 1: per-block shifted sums over items ----------------------
-// Items come from a float record [T][d][N] (item = t*N + c) or the FP64 state x [d][Np].
+// Items come from a float record [T][d][N] (item = t*N + c) or an FP64 array [d][pitch].
 // The shift is one vector s_i (spitch 0) or one per chain, s_i(c) = shift[i*spitch + c].
 // Slot p < d holds sum (v_i - s_i); slot d + pair(i, j), j <= i, holds sum of products.
-__global__ void moments_partial_kernel(const float* rec, const double* xs, int64_t T,
-                                       int64_t N, int64_t pitch, int d, const double* shift,
-                                       int64_t spitch, double* part) {
+//
+// For the covariance adaptation: a thread per slot over blocks of 128 items in LDS.  This order of
+// the sums is part of the adapted whitening's bits, hence of every later accept decision, so it
+// stays as it is (22 us for 6 x 81920 items, once per window).
+__global__ void adapt_moments_kernel(const float* rec, const double* xs, int64_t T, int64_t N,
+                                     int64_t pitch, int d, const double* shift, double* part) {
   constexpr int kChunk = 128;
   __shared__ double v[kChunk][kMaxD + 1];
   const int np = d + d * (d + 1) / 2;
@@ -148,7 +151,7 @@ __global__ void moments_partial_kernel(const float* rec, const double* xs, int64
       const int64_t t = it / N, c = it % N;
       for (int i = 0; i < d; ++i) {
         const double x = rec ? (double)rec[(t * d + i) * pitch + c] : xs[i * pitch + c];
-        v[threadIdx.x][i] = x - (spitch ? shift[i * spitch + c] : shift[i]);
+        v[threadIdx.x][i] = x - shift[i];
       }
     }
     __syncthreads();
@@ -185,81 +188,190 @@ __global__ void moments_partial_kernel(const float* rec, const double* xs, int64
   }
 }
 
-// Cholesky-Banachiewicz of a (d x d, row-major) into L; false if a pivot is not finite and
-// above `floor` (numerical positive definiteness).
-__device__ bool chol(const double* a, double* L, int d, double floor) {
-  for (int i = 0; i < d * d; ++i) L[i] = 0;
-  for (int i = 0; i < d; ++i) {
-    for (int j = 0; j <= i; ++j) {
-      double s = a[i * d + j];
-      for (int k = 0; k < j; ++k) s -= L[i * d + k] * L[j * d + k];
-      if (i == j) {
-        if (!(s > floor) || !isfinite(s)) return false;
-        L[i * d + i] = sqrt(s);
-      } else {
-        L[i * d + j] = s / L[j * d + j];
+// For the convergence metrics: the products are V^T V on FP64 MFMA (K = items): a wave takes 16
+// chains of one step at a time, a lane four consecutive chains of one parameter, which are its
+// operand of four MFMAs as A and as B alike.  D16 is the number of 16-parameter blocks (one product
+// tile, or three); VEC: N is a multiple of 4, so a lane's chains are one load.  Bound by the matrix
+// rate, 3 x 64 cycles per 4 items at d > 16, and the record's bytes: 27 x 1048576 items 59 us,
+// against 670 us with two LDS reads per product.
+constexpr int kMomWaves = 16;
+template <int D16, bool REC, bool VEC>
+__global__ __launch_bounds__(64 * kMomWaves) void moments_partial_kernel(
+    const float* rec, const double* xs, int64_t T, int64_t N, int64_t pitch, int d,
+    const double* shift, int64_t spitch, double* part) {
+  constexpr int NT = D16 * (D16 + 1) / 2;  // product tiles (a, b), b <= a
+  __shared__ double sh[NT * 256 + D16 * 16];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, g = lane >> 4, cl = lane & 15;
+  const int64_t per_t = (N + 15) / 16, chunks = T * per_t;
+  f64x4 acc[NT] = {};
+  double sum[D16] = {};
+  for (int64_t q = blockIdx.x * (int64_t)kMomWaves + wv; q < chunks;
+       q += (int64_t)gridDim.x * kMomWaves) {
+    const int64_t t = q / per_t, c = (q % per_t) * 16 + 4 * g;
+    double v[D16][4];
+#pragma unroll
+    for (int b = 0; b < D16; ++b) {
+      const int i = b * 16 + cl, ii = i < d ? i : d - 1;
+      if constexpr (VEC && REC) {
+        const bool in = i < d && c < N;
+        const int64_t cc = c < N ? c : N - 4;
+        float x[4];
+        double s[4];
+        __builtin_memcpy(x, rec + (t * d + ii) * pitch + cc, 16);
+        if (spitch) __builtin_memcpy(s, shift + ii * spitch + cc, 32);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[b][r] = in ? (double)x[r] - (spitch ? s[r] : shift[ii]) : 0.0;
+        continue;
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t cc = c + r < N ? c + r : N - 1;
+        const double x = REC ? (double)rec[(t * d + ii) * pitch + cc] : xs[ii * pitch + cc];
+        const double s = spitch ? shift[ii * spitch + cc] : shift[ii];
+        v[b][r] = i < d && c + r < N ? x - s : 0.0;
       }
     }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      int k = 0;
+#pragma unroll
+      for (int a = 0; a < D16; ++a)
+#pragma unroll
+        for (int b = 0; b <= a; ++b, ++k)
+          acc[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[a][r], v[b][r], acc[k], 0, 0, 0);
+#pragma unroll
+      for (int b = 0; b < D16; ++b) sum[b] += v[b][r];
+    }
   }
-  return true;
+#pragma unroll
+  for (int b = 0; b < D16; ++b) sum[b] = sum_lane_groups(sum[b]);
+  // the waves add their tiles in order; D slot r of a lane is (row g + 4 r, column cl)
+  for (int w = 0; w < kMomWaves; ++w) {
+    if (wv == w) {
+#pragma unroll
+      for (int k = 0; k < NT; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          double* o = sh + k * 256 + (g + 4 * r) * 16 + cl;
+          *o = w ? *o + acc[k][r] : acc[k][r];
+        }
+      if (g == 0) {
+#pragma unroll
+        for (int b = 0; b < D16; ++b) {
+          double* o = sh + NT * 256 + b * 16 + cl;
+          *o = w ? *o + sum[b] : sum[b];
+        }
+      }
+    }
+    __syncthreads();
+  }
+  const int np = d + d * (d + 1) / 2;
+  for (int p = tid; p < np; p += 64 * kMomWaves) {
+    double v;
+    if (p < d) {
+      v = sh[NT * 256 + p];
+    } else {
+      int q = p - d, i = 0;
+      while (q > i) {
+        q -= i + 1;
+        ++i;
+      }
+      const int a = i >> 4, b = q >> 4;
+      v = sh[(a * (a + 1) / 2 + b) * 256 + (i & 15) * 16 + (q & 15)];
+    }
+    part[(int64_t)blockIdx.x * np + p] = v;
+  }
+}
+
+// Cholesky factor of a (d x d, row-major, LDS) into L by columns, one thread per row (every thread
+// of the workgroup calls; the sums run over k in order); false if a pivot is not finite and above
+// `floor` (numerical positive definiteness).
+__device__ bool chol(const double* a, double* L, int d, double floor, int* bad) {
+  const int i = threadIdx.x;
+  for (int e = i; e < d * d; e += kAuxThreads) L[e] = 0;
+  if (i == 0) *bad = 0;
+  __syncthreads();
+  for (int j = 0; j < d; ++j) {
+    double s = 0;
+    if (i >= j && i < d) {
+      s = a[i * d + j];
+      for (int k = 0; k < j; ++k) s -= L[i * d + k] * L[j * d + k];
+      if (i == j) {
+        if (!(s > floor) || !isfinite(s)) *bad = 1;
+        L[j * d + j] = sqrt(s);
+      }
+    }
+    __syncthreads();
+    if (*bad) break;
+    if (i > j && i < d) L[i * d + j] = s / L[j * d + j];
+    __syncthreads();
+  }
+  const bool ok = *bad == 0;
+  __syncthreads();
+  return ok;
 }
 
 // Pass 2 (one block): mean, covariance, symmetrise, jittered Cholesky; on success writes
 // the new whitening.  info = [status (0 ok / 1 not PD), jitter, logdet].
-__global__ void moments_final_kernel(const double* part, int nblocks, int64_t count, int d,
-                                     const double* shift, int update_mean, double* mu,
-                                     double* Lout, double* info) {
+// The partial sums are added in block order, sixteen loads ahead.
+__global__ __launch_bounds__(kAuxThreads) void moments_final_kernel(
+    const double* part, int nblocks, int64_t count, int d, const double* shift, int update_mean,
+    double* mu, double* Lout, double* info) {
+  constexpr int kMaxP = kMaxD + kMaxD * (kMaxD + 1) / 2;
   __shared__ double S[kMaxD * kMaxD];
   __shared__ double Lt[kMaxD * kMaxD];
-  __shared__ double sum[kMaxD + kMaxD * (kMaxD + 1) / 2];
-  const int np = d + d * (d + 1) / 2;
-  for (int p = threadIdx.x; p < np; p += kAuxThreads) {
+  __shared__ double sum[kMaxP];
+  __shared__ double diag[kMaxD];
+  __shared__ int bad;
+  const int tid = threadIdx.x, np = d + d * (d + 1) / 2;
+  for (int p = tid; p < np; p += kAuxThreads) {
     double s = 0;
-    for (int b = 0; b < nblocks; ++b) s += part[(int64_t)b * np + p];
+    for (int b0 = 0; b0 < nblocks; b0 += 16) {
+      double v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u] = part[(int64_t)(b0 + u < nblocks ? b0 + u : b0) * np + p];
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        if (b0 + u < nblocks) s += v[u];
+    }
     sum[p] = s;
   }
   __syncthreads();
-  if (threadIdx.x != 0) return;
   const double n = (double)count;
-  int q = d;
-  for (int i = 0; i < d; ++i)
-    for (int j = 0; j <= i; ++j, ++q) {
-      const double c = (sum[q] - sum[i] * sum[j] / n) / (n - 1.0);
-      S[i * d + j] = c;
-      S[j * d + i] = c;
-    }
-  for (int i = 0; i < d; ++i)
-    for (int j = 0; j < i; ++j) {
-      const double c = 0.5 * (S[i * d + j] + S[j * d + i]);
-      S[i * d + j] = S[j * d + i] = c;
-    }
+  for (int e = tid; e < d * d; e += kAuxThreads) {
+    const int i = e / d > e % d ? e / d : e % d, j = e / d > e % d ? e % d : e / d;
+    const double c = (sum[d + i * (i + 1) / 2 + j] - sum[i] * sum[j] / n) / (n - 1.0);
+    S[e] = c;
+    if (i == j) diag[i] = c;
+  }
+  __syncthreads();
   double jit = 0, scale = 0;
-  for (int i = 0; i < d; ++i) scale += S[i * d + i];
+  for (int i = 0; i < d; ++i) scale += diag[i];
   scale /= d;
   const double floor = isfinite(scale) ? 1e-12 * scale : 0.0;  // pivot floor
-  bool ok = chol(S, Lt, d, floor);
-  if (!ok) {
-    double S0[kMaxD];
-    for (int i = 0; i < d; ++i) S0[i] = S[i * d + i];
-    for (double lam = 1e-10; lam <= 1e-2 * (1 + 1e-12) && !ok; lam *= 10.0) {
-      jit = lam * scale;
-      for (int i = 0; i < d; ++i) S[i * d + i] = S0[i] + jit;
-      ok = chol(S, Lt, d, floor);
-    }
+  bool ok = chol(S, Lt, d, floor, &bad);
+  for (double lam = 1e-10; lam <= 1e-2 * (1 + 1e-12) && !ok; lam *= 10.0) {
+    jit = lam * scale;
+    if (tid < d) S[tid * d + tid] = diag[tid] + jit;
+    __syncthreads();
+    ok = chol(S, Lt, d, floor, &bad);
   }
   if (!ok) {
-    info[0] = 1;
-    info[1] = jit;
+    if (tid == 0) {
+      info[0] = 1;
+      info[1] = jit;
+    }
     return;
   }
-  double ld = 0;
-  for (int i = 0; i < d; ++i) ld += log(Lt[i * d + i]);
-  for (int i = 0; i < d * d; ++i) Lout[i] = Lt[i];
-  if (update_mean)
-    for (int i = 0; i < d; ++i) mu[i] = shift[i] + sum[i] / n;
-  info[0] = 0;
-  info[1] = jit;
-  info[2] = ld;
+  for (int e = tid; e < d * d; e += kAuxThreads) Lout[e] = Lt[e];
+  if (update_mean && tid < d) mu[tid] = shift[tid] + sum[tid] / n;
+  if (tid == 0) {
+    double ld = 0;
+    for (int i = 0; i < d; ++i) ld += log(Lt[i * d + i]);
+    info[0] = 0;
+    info[1] = jit;
+    info[2] = ld;
+  }
 }
 
 // ---- ESS ----------------------------------------------------------------------------------
@@ -759,23 +871,34 @@ hipError_t launch_aies_record(const State& S, int d, float* rec, int64_t slot, i
   return hipGetLastError();
 }
 
-hipError_t launch_moments(const float* rec, const double* xs, int64_t T, int64_t N,
-                          int64_t pitch, int d, const double* shift, double* part, int nblocks,
-                          int update_mean, double* mu, double* L, double* info, hipStream_t s) {
-  hipLaunchKernelGGL(moments_partial_kernel, dim3(nblocks), dim3(kAuxThreads), 0, s, rec, xs, T,
-                     N, pitch, d, shift, (int64_t)0, part);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(moments_final_kernel, dim3(1), dim3(kAuxThreads), 0, s, part, nblocks,
-                     T * N, d, shift, update_mean, mu, L, info);
-  return hipGetLastError();
-}
-
 hipError_t launch_moment_sums(const float* rec, const double* xs, int64_t T, int64_t N,
                               int64_t pitch, int d, const double* shift, int64_t spitch,
                               double* part, int nblocks, hipStream_t s) {
-  hipLaunchKernelGGL(moments_partial_kernel, dim3(nblocks), dim3(kAuxThreads), 0, s, rec, xs, T,
-                     N, pitch, d, shift, spitch, part);
+  const dim3 g(nblocks), b(64 * kMomWaves);
+  const bool vec = N % 4 == 0;
+#define BEST_MOMENTS(D16)                                                                        \
+  if (!rec) hipLaunchKernelGGL((moments_partial_kernel<D16, false, false>), g, b, 0, s, rec, xs, \
+                               T, N, pitch, d, shift, spitch, part);                             \
+  else if (vec) hipLaunchKernelGGL((moments_partial_kernel<D16, true, true>), g, b, 0, s, rec,   \
+                                   xs, T, N, pitch, d, shift, spitch, part);                     \
+  else hipLaunchKernelGGL((moments_partial_kernel<D16, true, false>), g, b, 0, s, rec, xs, T, N, \
+                          pitch, d, shift, spitch, part)
+  if (d <= 16) {
+    BEST_MOMENTS(1);
+  } else {
+    BEST_MOMENTS(2);
+  }
+#undef BEST_MOMENTS
+  return hipGetLastError();
+}
+
+hipError_t launch_moments(const float* rec, const double* xs, int64_t T, int64_t N,
+                          int64_t pitch, int d, const double* shift, double* part, int nblocks,
+                          int update_mean, double* mu, double* L, double* info, hipStream_t s) {
+  hipLaunchKernelGGL(adapt_moments_kernel, dim3(nblocks), dim3(kAuxThreads), 0, s, rec, xs, T, N,
+                     pitch, d, shift, part);
+  hipLaunchKernelGGL(moments_final_kernel, dim3(1), dim3(kAuxThreads), 0, s, part, nblocks,
+                     T * N, d, shift, update_mean, mu, L, info);
   return hipGetLastError();
 }
 
