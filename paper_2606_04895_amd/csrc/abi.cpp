@@ -249,6 +249,10 @@ static int run_eval(best_ctx* h, const double* X, int64_t pitch, int64_t n, doub
   a.ex_lp = LP;
   a.ex_g = G;
   a.ex_grad = G != nullptr;
+  if (a.tg.plain_mode == 2 && !G) {
+    HIPCHK(h, launch_plain_eval(a, h->stream));
+    return BEST_OK;
+  }
   int mt = h->MT, grid_cap = h->grid_cap;
   size_t lds = h->lds.total;
   if (!h->mt_fixed) {
@@ -470,6 +474,33 @@ static int upload_problem(best_ctx* h, const best_problem* p) {
     HIPCHK(h, m.upload((double**)&t.pg0, pm->gamma0, nt, s));
     HIPCHK(h, m.upload((double**)&t.pc, pm->center, d, s));
     HIPCHK(h, m.upload((double**)&t.pis, pm->invscale, d, s));
+    // tables of the recurrence over the bins (see plain_wave).  The grid counts as even where no
+    // point is further from x_0 + j h than rounding puts it (two ulps of the largest)
+    double xm = 0, off = 0;
+    const double x0 = pm->xgrid[0], hx = nb > 1 ? (pm->xgrid[nb - 1] - x0) / (double)(nb - 1) : 0.0;
+    for (size_t j = 0; j < nb; ++j) {
+      xm = std::max(xm, std::fabs(pm->xgrid[j]));
+      off = std::max(off, std::fabs(pm->xgrid[j] - (x0 + (double)j * hx)));
+    }
+    t.pl_even = off <= xm * 0x1p-51 ? 1 : 0;
+    t.pl_step = 64.0 * hx;
+    auto turn = [](double k, double x, double* out) {  // cos, sin of 2 pi k x
+      long double f = (long double)k * x;
+      f = 2.0L * 3.141592653589793238462643383279503L * (f - roundl(f));
+      out[0] = (double)cosl(f);
+      out[1] = (double)sinl(f);
+    };
+    const size_t seg = 64 * kPlainSeg, n_seg = (nb + seg - 1) / seg;
+    std::vector<double> rot(2 * nt), trig(n_seg * kMaxTerms * 64 * 2, 0.0);
+    for (size_t q = 0; q < nt; ++q) {
+      turn(pm->k[q], t.pl_step, &rot[2 * q]);
+      for (size_t g = 0; g < n_seg; ++g)
+        for (size_t l = 0; l < 64 && g * seg + l < nb; ++l)
+          turn(pm->k[q], pm->xgrid[g * seg + l], &trig[((g * kMaxTerms + q) * 64 + l) * 2]);
+    }
+    HIPCHK(h, m.upload((double**)&t.pl_rot, rot.data(), rot.size(), s));
+    HIPCHK(h, m.upload((double**)&t.pl_trig, trig.data(), trig.size(), s));
+    HIPCHK(h, hipStreamSynchronize(s));  // the tables are local
   }
   h->lower.assign(p->lower, p->lower + d);
   h->upper.assign(p->upper, p->upper + d);

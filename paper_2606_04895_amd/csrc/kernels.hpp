@@ -21,6 +21,10 @@ struct Target {
   const double *train_lo, *train_hi;
   int n_bins, n_terms;
   const double *xgrid, *data, *w2, *pa, *pg, *pp, *pk, *pg0, *pc, *pis;
+  int pl_even;            // the grid is evenly spaced: the recurrence of plain_wave applies
+  double pl_step;         // 64 grid spacings
+  const double* pl_rot;   // [n_terms][2] cos, sin of 2 pi k over pl_step
+  const f64x2* pl_trig;   // [segments][kMaxTerms][64] cos, sin of 2 pi k x at a segment's first bins
   int box_penalty;  // 1: smooth penalty outside the prior box instead of -inf
   double pen_w;     // its width w (in box widths)
 };
@@ -187,7 +191,8 @@ struct KArgs {
 };
 
 // ---------------------------------------------------------------------------------------
-// Plain spectrum log-likelihood of one chain, computed by the whole workgroup.
+// Plain spectrum log-likelihood of one chain.  With its gradient: computed by the whole
+// workgroup, an exponential, a sine and a cosine per bin and term.
 // ---------------------------------------------------------------------------------------
 // Element (i, c) of a tile's [d][M] FP64 array: the global SoA state (p = base + c0,
 // pitch = Np), a caller's array, or the tile's LDS scratch (pitch = M).
@@ -321,6 +326,111 @@ __device__ __forceinline__ void plain_chain(const Target& tg, const TView& X, in
     outg[tid] = -dt * tg.pis[tid];
   }
   __syncthreads();
+}
+
+// v of lane m (m the same in every lane), as a scalar.
+__device__ __forceinline__ double lane_value(double v, int m) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, m);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), m);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// Plain spectrum log-likelihood of one chain by one wave, without the gradient (training data,
+// importance weights, MH and the ensemble moves); lane l takes bins l, l + 64, ...  Term m's amplitude times its damped oscillation, as a complex number
+//   w_m(j) = a_m exp(-gamma_m x_j) exp(i (2 pi k_m x_j + phi_m)),
+// advances over an evenly spaced grid by one complex factor z_m per 64 bins, so a bin costs
+// four FP64 multiply-adds per term instead of an exponential and a sine and cosine.  Each lane
+// starts from its first bin (exp(-gamma x), and the chain-independent cos / sin(2 pi k x) from a
+// table) and restarts from the bin itself every kPlainSeg steps, so that rounding grows over at
+// most that many factors: below the rounding of the phase 2 pi k x + phi itself (half an ulp of 150
+// rad at k = 24).  Bound by the FP64 rate: 20000 points, 2500 bins x 8 terms 318 us in the tile
+// kernels (plain_eval_kernel: 121 us), against 3550 us with exp and sincos per bin and a workgroup
+// per chain.  A grid that is not evenly spaced evaluates every bin directly.
+constexpr int kPlainSeg = 64;
+__device__ __forceinline__ void plain_wave(const Target& tg, const TView& X, int c, double* outv) {
+  constexpr double kPi = 3.141592653589793;
+  const int lane = local_tid() & 63, d = tg.d, nt = tg.n_terms, nb = tg.n_bins;
+  const int li = lane < d ? lane : d - 1, lm = lane < nt ? lane : nt - 1;
+  // lane i: the scaled component i; lane m: term m
+  const double tl = (X(li, c) - tg.pc[li]) * tg.pis[li];
+  double sa = 0, sg = 0, sp = 0;
+  for (int i = 0; i < d; ++i) {
+    const double ti = lane_value(tl, i);
+    sa += tg.pa[lm * d + i] * ti;
+    sg += tg.pg[lm * d + i] * ti;
+    sp += tg.pp[lm * d + i] * ti;
+  }
+  const bool own = lane < nt;
+  const double th = tanh(sp), A = own ? exp(sa) : 0.0, gm = own ? tg.pg0[lm] * exp(sg) : 0.0;
+  double sph, cph;
+  sincos(kPi * th, &sph, &cph);
+  const double ez = own ? exp(-gm * tg.pl_step) : 0.0;
+  const double Pl = A * cph, Ql = A * sph, zrl = ez * tg.pl_rot[2 * lm], zil = ez * tg.pl_rot[2 * lm + 1];
+  double P[kMaxTerms], Q[kMaxTerms], ga[kMaxTerms], zr[kMaxTerms], zi[kMaxTerms];
+#pragma unroll
+  for (int m = 0; m < kMaxTerms; ++m) {
+    P[m] = lane_value(Pl, m);
+    Q[m] = lane_value(Ql, m);
+    ga[m] = lane_value(gm, m);
+    zr[m] = lane_value(zrl, m);
+    zi[m] = lane_value(zil, m);
+  }
+  double ll = 0, re[kMaxTerms], im[kMaxTerms];
+  // terms past n_terms have P = Q = z = 0 and stay zero
+  auto seed = [&](int j, bool table) {
+    const double x = tg.xgrid[j];
+#pragma unroll
+    for (int m = 0; m < kMaxTerms; ++m) {
+      double cs, sn;
+      if (table) {
+        const f64x2 t = tg.pl_trig[((int64_t)(j / (64 * kPlainSeg)) * kMaxTerms + m) * 64 + (j & 63)];
+        cs = t[0];
+        sn = t[1];
+      } else {
+        sincos(2.0 * kPi * tg.pk[m < nt ? m : nt - 1] * x, &sn, &cs);
+      }
+      const double e = exp(-ga[m] * x);
+      re[m] = e * (cs * P[m] - sn * Q[m]);
+      im[m] = e * (sn * P[m] + cs * Q[m]);
+    }
+  };
+  auto bin = [&](int j, bool valid, double dat, double w2) {
+    double spec = 0;
+#pragma unroll
+    for (int m = 0; m < kMaxTerms; ++m) spec += re[m];
+    const double dr = valid ? spec - dat : 0.0, r = dr * w2;
+    ll += dr * r;
+  };
+  if (tg.pl_even) {
+    for (int j0 = 0; j0 < nb; j0 += 64 * kPlainSeg) {
+      seed(j0 + lane < nb ? j0 + lane : nb - 1, true);
+      const int j1 = j0 + 64 * kPlainSeg < nb ? j0 + 64 * kPlainSeg : nb;
+      double dat = tg.data[j0 + lane < nb ? j0 + lane : nb - 1];
+      double w2 = tg.w2[j0 + lane < nb ? j0 + lane : nb - 1];
+      for (int jb = j0; jb < j1; jb += 64) {
+        const int j = jb + lane, jn = j + 64 < nb ? j + 64 : nb - 1;
+        const double dn = tg.data[jn], wn = tg.w2[jn];
+        bin(j, j < nb, dat, w2);
+        dat = dn;
+        w2 = wn;
+#pragma unroll
+        for (int m = 0; m < kMaxTerms; ++m) {
+          const double t = re[m] * zr[m] - im[m] * zi[m];
+          im[m] = im[m] * zr[m] + re[m] * zi[m];
+          re[m] = t;
+        }
+      }
+    }
+  } else {
+    for (int jb = 0; jb < nb; jb += 64) {
+      const int j = jb + lane, jj = j < nb ? j : nb - 1;
+      seed(jj, false);
+      bin(j, j < nb, tg.data[jj], tg.w2[jj]);
+    }
+  }
+  ll = wave_sum(ll);
+  if (lane == 0) *outv = -0.5 * ll;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -959,8 +1069,14 @@ __device__ __forceinline__ void eval_tile(const KArgs& a, char* smem, typename P
   double* pgr = pv + M;        // [M][d]
   double* psc = pgr + M * d;   // plain scratch
   if (tg.plain_mode != 0) {
-    for (int c = 0; c < mv; ++c) {
-      if (!intrain[c]) plain_chain(tg, X, c, grad, psc, pv + c, pgr + c * d);
+    if (grad) {
+      for (int c = 0; c < mv; ++c)
+        if (!intrain[c]) plain_chain(tg, X, c, true, psc, pv + c, pgr + c * d);
+    } else {
+      const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+      for (int c = wv; c < mv; c += kWaves)
+        if (!__builtin_amdgcn_readfirstlane(intrain[c])) plain_wave(tg, X, c, pv + c);
+      __syncthreads();
     }
   }
   if constexpr (kWide<MT> && IsWidePost<Post>::value) {

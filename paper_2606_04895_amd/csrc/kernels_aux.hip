@@ -583,6 +583,48 @@ hipError_t noalloc_scratch_address(int dev, double** p) {
   return hipSuccess;
 }
 
+// ---- batch log pi of the plain model (no gradient): one wave per point -----------------------
+// The tile kernels hold a workgroup per CU with the registers of the emulator passes, one wave per
+// SIMD; here several waves share one, which hides the latency of plain_wave's dependent FP64
+// chains: 20000 points of the 2500-bin model 121 us, against 318 us in 64-point tiles.  The sums of
+// the Gaussian part and of the penalty keep the tile kernels' component order.
+__global__ __launch_bounds__(kAuxThreads) void plain_eval_kernel(KArgs a) {
+  const Target& tg = a.tg;
+  const int64_t c = (int64_t)blockIdx.x * (kAuxThreads / 64) + (threadIdx.x >> 6);
+  if (c >= a.st.N) return;
+  const int lane = threadIdx.x & 63, d = tg.d, i = lane < d ? lane : d - 1;
+  __shared__ double out[kAuxThreads / 64];
+  double* pl = out + (threadIdx.x >> 6);
+  const TView X{const_cast<double*>(a.ex_x) + c, a.ex_pitch};
+  plain_wave(tg, X, 0, pl);
+  const double x = X(i, 0);
+  const bool in = __ballot(lane < d && !(x >= tg.lower[i] && x <= tg.upper[i])) == 0;
+  double lp = tg.offset;
+  if (tg.gauss_coef != 0.0) {
+    double y = x;
+    if (tg.tw_v >= 0) {
+      const double du = lane_value(x, tg.tw_u) - tg.tw_center;
+      if (i == tg.tw_v) y = y + tg.tw_beta * (du * du - tg.tw_kappa);
+    }
+    const double R = y - tg.gmean[i];
+    double PR = 0, q = 0;
+    for (int j = 0; j < d; ++j) PR += tg.gprec[i * d + j] * lane_value(R, j);
+    for (int j = 0; j < d; ++j) q += lane_value(R, j) * lane_value(PR, j);
+    lp += tg.gauss_coef * (-0.5 * q);
+  }
+  lp += lane_value(lane == 0 ? *pl : 0.0, 0);
+  if (tg.box_penalty) {
+    if (!in) {
+      double dp;
+      const double pen = box_pen(tg, i, x, &dp);
+      for (int j = 0; j < d; ++j) lp -= lane_value(pen, j);
+    }
+  } else if (!in) {
+    lp = -INFINITY;
+  }
+  if (lane == 0) a.ex_lp[c] = lp;
+}
+
 // ---- layout conversion: dst[j][i] = src[i][j] for a rows x cols row-major source ----------
 __global__ void transpose_kernel(const double* src, int64_t rows, int64_t cols, double* dst) {
   const int64_t total = rows * cols;
@@ -932,6 +974,13 @@ hipError_t launch_ess_autocov(const float* rec, const double* mean, int64_t T, i
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(ess_sum_kernel, dim3((unsigned)d, (unsigned)n_win), dim3(8 * kEssLB), 0, s, part,
                      nblk * n_seg, n_win * kEssLB, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_plain_eval(const KArgs& a, hipStream_t s) {
+  constexpr int64_t w = kAuxThreads / 64;
+  hipLaunchKernelGGL(plain_eval_kernel, dim3((unsigned)((a.st.N + w - 1) / w)), dim3(kAuxThreads), 0, s,
+                     a);
   return hipGetLastError();
 }
 
