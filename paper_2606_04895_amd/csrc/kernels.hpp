@@ -1013,7 +1013,6 @@ __device__ __forceinline__ void eval_tile(const KArgs& a, char* smem, typename P
   s.red = (acc*)(smem + L.red);
   s.outp = (acc*)(smem + L.outp);
   s.out = (acc*)(smem + L.out);
-  s.up = nullptr;
   int* inbox = (int*)(smem + L.mi);
   int* intrain = inbox + M;
 
@@ -1056,8 +1055,8 @@ __device__ __forceinline__ void eval_tile(const KArgs& a, char* smem, typename P
 
   // the input layer joins the barrier that publishes the inputs and flags
   if (tg.plain_mode != 2) {
-    mlp_forward<P, MT>(a.mp, s, hsave, nullptr, grad, true, grad);
-    if (grad) mlp_backward<P, MT>(a.mp, s, hsave, nullptr, true, true, true);
+    mlp_forward<P, MT>(a.mp, s, hsave, grad, true, grad);
+    if (grad) mlp_backward<P, MT>(a.mp, s, hsave);
   } else {
     __syncthreads();
   }
