@@ -1338,11 +1338,11 @@ __device__ __forceinline__ void flush_tally(const State& S, int64_t ch, const Ta
   S.step_prob[ch] = ty.last_prob;
 }
 
-// Accept bookkeeping for chain ch of the tile (called by one thread per chain).
-__device__ __forceinline__ bool decide(const KArgs& a, Tally& ty, int64_t ch, uint64_t t,
-                                       uint32_t sub, double la, double lpp, int inbox) {
-  const double u = accept_uniform(a.rng, ch, t, sub);
-  const bool acc = log(u) < la;
+// Accept bookkeeping of one chain for acceptance uniform u with logarithm log_u (called by one
+// thread per chain).
+__device__ __forceinline__ bool decide_at(Tally& ty, double log_u, double la, double lpp,
+                                          int inbox) {
+  const bool acc = log_u < la;
   const double pr = accept_prob(la);
   ty.acc += acc ? 1u : 0u;
   ty.sum_prob += pr;
@@ -1350,6 +1350,12 @@ __device__ __forceinline__ bool decide(const KArgs& a, Tally& ty, int64_t ch, ui
   ty.nonfinite += isnan(lpp) ? 1u : 0u;
   ty.oob += inbox ? 0u : 1u;
   return acc;
+}
+
+// The same for chain ch of the tile, with its uniform drawn here.
+__device__ __forceinline__ bool decide(const KArgs& a, Tally& ty, int64_t ch, uint64_t t,
+                                       uint32_t sub, double la, double lpp, int inbox) {
+  return decide_at(ty, log(accept_uniform(a.rng, ch, t, sub)), la, lpp, inbox);
 }
 
 __device__ __forceinline__ void record_tile(const KArgs& a, int s, int d, int M, int mv,
@@ -1381,12 +1387,133 @@ __device__ __forceinline__ void commit_tile(const State& S, const Scratch& T, co
 // ---------------------------------------------------------------------------------------
 // Transitions for one tile at global step t.
 // ---------------------------------------------------------------------------------------
+// Metropolis-Hastings on lane groups (the expressions of the loop form in mh_tile, in their
+// order).  A step of a small tile is a serial chain of FP64 latencies, not work: 16 chains of 6
+// parameters on 6 -> 128 x 2 in FP64 took 19.1 us a step as loops and take 14.5 here, of which the
+// matrix instructions need 1.8.  So no step waits for memory or for a barrier that the emulator does not need: the chains' points
+// and log pi stay in the tile's scratch (written through to the state when a move is accepted),
+// step s's normals and log u are drawn during step s - 1 by the waves that hold no chain, and the
+// decision, the commit and the record follow the evaluation in its continuation.
+// s counts the launch's steps for this tile.  The chain's tally lives in thread G c.
+template <class P, int MT, int G, int V>
+__device__ __forceinline__ void mh_gw(const KArgs& a, char* smem, typename P::acc* hsave,
+                                      Tally& ty, int64_t c0, int mv, uint64_t t, int s) {
+  constexpr int M = 16 * MT, kSpare = kThreads - G * M;
+  const State& S = a.st;
+  const int d = a.tg.d, tid = local_tid();
+  const Scratch T = tile_scratch<MT>(a, smem, c0);
+  const int* inbox = (const int*)(smem + a.lds.mi);
+  // current points in T.z, log pi in row 0 of T.zp; normals of even and odd steps in T.q and T.gz,
+  // log u in row 0 of T.gzp and T.gxp (values only: no gradient is written there)
+  const TView nz = (s & 1) ? T.gz : T.q, nzn = (s & 1) ? T.q : T.gz;
+  const TView lu = (s & 1) ? T.gxp : T.gzp, lun = (s & 1) ? T.gzp : T.gxp;
+  const bool drawn = kSpare > 0 && s > 0;
+  if (tid < G * M) {
+    const int c = tid / G, i = tid % G, gb = gw_base<G>(tid), cc = clampd(c, mv);
+    const bool valid = c < mv;
+    double x[V], z[V], zp[V], xp[V];
+#pragma unroll
+    for (int u = 0; u < V; ++u) {
+      const int k = i + G * u, kk = clampd(k, d);
+      const bool act = valid && k < d;
+      double xr;
+      if (s > 0) {
+        xr = T.z(kk, cc);
+      } else {
+        xr = S.x[kk * S.Np + c0 + cc];
+        if (act) T.z(k, c) = xr;
+      }
+      x[u] = act ? xr : 0.0;
+    }
+    if (s == 0 && valid && i == 0) T.zp(0, c) = S.lp[c0 + c];
+    gw_whiten<G, V>(a.wh.mu, a.wh.L, d, i, gb, x, z);
+#pragma unroll
+    for (int u = 0; u < V; ++u) {
+      const int k = i + G * u;
+      zp[u] = 0.0;
+      if (valid && k < d) {
+        const double sc = a.step_mult ? a.mh_scale * a.step_mult[k] : a.mh_scale;
+        const double n =
+            drawn ? nz(k, c) : normal_dim(a.rng, c0 + c, t, kStreamNormal, 0, k);
+        zp[u] = z[u] + sc * n;
+      }
+    }
+    gw_affine<G, V>(a.wh.mu, a.wh.L, d, i, gb, zp, xp);
+#pragma unroll
+    for (int u = 0; u < V; ++u)
+      if (valid && i + G * u < d) T.xp(i + G * u, c) = xp[u];
+    gw_stage<P, MT, G, V>(a, smem, c, i, valid, xp);
+  } else if (s + 1 < a.n_steps) {
+    for (int e = tid - G * M; e < (d + 1) * M; e += kSpare > 0 ? kSpare : 1) {
+      const int i = e / M, c = e % M;
+      if (c >= mv) continue;
+      if (i < d) nzn(i, c) = normal_dim(a.rng, c0 + c, t + 1, kStreamNormal, 0, i);
+      else lun(0, c) = log(accept_uniform(a.rng, c0 + c, t + 1, 0));
+    }
+  }
+  bool rec = false;
+  int64_t slot = 0;
+  if (a.record) {
+    const int64_t sc = a.rec_s0 + s + 1;
+    slot = sc / a.thin - 1;
+    rec = sc % a.thin == 0 && slot < a.rec_cap;
+  }
+  // eval_tile instantiates both lane-group forms; only the one with this V runs
+  auto post = [&](int c, int i, bool valid, const auto& xn, const auto&, double lp) {
+    if constexpr (sizeof(xn) == V * sizeof(double)) {
+      const int gb = gw_base<G>(local_tid()), cc = clampd(c, mv);
+      double x[V], xc[V];
+      __builtin_memcpy(x, &xn, sizeof(x));
+#pragma unroll
+      for (int u = 0; u < V; ++u) xc[u] = T.z(clampd(i + G * u, d), cc);
+      int acc = 0;
+      if (valid && i == 0) {
+        const double log_u = drawn ? lu(0, c) : log(accept_uniform(a.rng, c0 + c, t, 0));
+        acc = decide_at(ty, log_u, lp - T.zp(0, c), lp, inbox[c]) ? 1 : 0;
+        if (acc) {
+          T.zp(0, c) = lp;
+          S.lp[c0 + c] = lp;
+        }
+      }
+      acc = __builtin_amdgcn_ds_bpermute(gb, acc);  // chain c's decision, from thread G c
+#pragma unroll
+      for (int u = 0; u < V; ++u) {
+        const int k = i + G * u;
+        if (valid && k < d) {
+          if (acc) {
+            T.z(k, c) = x[u];
+            S.x[k * S.Np + c0 + c] = x[u];
+          }
+          if (rec) a.record[(slot * d + k) * a.rec_pitch + c0 + c] = (float)(acc ? x[u] : xc[u]);
+        }
+      }
+    }
+  };
+  if constexpr (V == 1)
+    eval_tile<P, MT>(a, smem, hsave, T.xp, mv, T.lpp, T.gxp, false, true, true, post);
+  else
+    eval_tile<P, MT>(a, smem, hsave, T.xp, mv, T.lpp, T.gxp, false, true, true,
+                     WidePost<decltype(post)>{post});
+}
+
 template <class P, int MT>
 __device__ __forceinline__ void mh_tile(const KArgs& a, char* smem, typename P::acc* hsave,
-                                        Tally& ty, int64_t c0, int mv, uint64_t t) {
+                                        Tally& ty, int64_t c0, int mv, uint64_t t, int s) {
   constexpr int M = 16 * MT;
   const State& S = a.st;
   const int d = a.tg.d, tid = local_tid();
+  if constexpr (8 * M <= kThreads) {
+    if (group_path<P, MT>(a)) {
+      mh_gw<P, MT, 8, 1>(a, smem, hsave, ty, c0, mv, t, s);
+      return;
+    }
+  }
+  if constexpr (kWide<MT> && 16 * M <= kThreads) {
+    if (wide_path<P, MT>(a)) {
+      mh_gw<P, MT, 16, 2>(a, smem, hsave, ty, c0, mv, t, s);
+      return;
+    }
+  }
   const Scratch T = tile_scratch<MT>(a, smem, c0);
   int* inbox = (int*)(smem + a.lds.mi);
   int* flag = inbox + 2 * M;
@@ -1394,8 +1521,8 @@ __device__ __forceinline__ void mh_tile(const KArgs& a, char* smem, typename P::
   for (int e = tid; e < d * M; e += kThreads) {
     const int i = e / M, c = e % M;
     if (c >= mv) continue;
-    const double s = a.step_mult ? a.mh_scale * a.step_mult[i] : a.mh_scale;
-    T.zp(i, c) = T.z(i, c) + s * normal_dim(a.rng, c0 + c, t, kStreamNormal, 0, i);
+    const double sc = a.step_mult ? a.mh_scale * a.step_mult[i] : a.mh_scale;
+    T.zp(i, c) = T.z(i, c) + sc * normal_dim(a.rng, c0 + c, t, kStreamNormal, 0, i);
   }
   __syncthreads();
   tile_affine(a.wh.mu, a.wh.L, d, M, mv, T.zp, T.xp);
@@ -1412,6 +1539,7 @@ __device__ __forceinline__ void mh_tile(const KArgs& a, char* smem, typename P::
   __syncthreads();
   commit_tile(S, T, flag, d, M, mv, c0, false);
   __syncthreads();
+  record_tile(a, s, d, M, mv, c0);
 }
 
 // MALA on wide lane groups (the expressions of the loop form in mala_tile, in their order):
@@ -2368,19 +2496,19 @@ __global__ __launch_bounds__(kThreads, 1) void step_kernel(KArgs a) {
     Tally ty{};
     for (int s = 0; s < a.n_steps; ++s) {
       const uint64_t t = (uint64_t)(a.step0 + s);
-      if constexpr (SAMPLER == 0) mh_tile<P, MT>(a, smem, hsave, ty, c0, mv, t);
+      if constexpr (SAMPLER == 0) mh_tile<P, MT>(a, smem, hsave, ty, c0, mv, t, s);
       if constexpr (SAMPLER == 1) mala_tile<P, MT>(a, smem, hsave, ty, c0, mv, t, eps);
       if constexpr (SAMPLER == 2) hmc_tile<P, MT>(a, smem, hsave, ty, c0, mv, t, eps);
       if constexpr (SAMPLER == 3) aies_tile<P, MT>(a, smem, hsave, ty, c0, mv, t);
       if constexpr (SAMPLER == 4) nuts_tile<P, MT>(a, smem, hsave, c0, mv, t, eps);
       if constexpr (SAMPLER == 5) de_tile<P, MT>(a, smem, hsave, ty, c0, mv, t);
-      if constexpr (!kHalves) record_tile(a, s, a.tg.d, M, mv, c0);
+      if constexpr (SAMPLER != 0 && !kHalves) record_tile(a, s, a.tg.d, M, mv, c0);
     }
     if constexpr (SAMPLER != 4) {
-      // the lane-group MALA / HMC keep chain c's tally in thread G c (G = 8 or 16), the
+      // the lane-group MH / MALA / HMC keep chain c's tally in thread G c (G = 8 or 16), the
       // others in thread c
       int own = 1;
-      if constexpr (SAMPLER == 1 || SAMPLER == 2) {
+      if constexpr (SAMPLER <= 2) {
         if (group_path<P, MT>(a)) own = 8;
         else if (wide_path<P, MT>(a)) own = 16;
       }
