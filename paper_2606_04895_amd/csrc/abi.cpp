@@ -20,6 +20,7 @@ namespace best {
   hipError_t launch_step_##suf(int, const KArgs&, int, size_t, hipStream_t);                 \
   hipError_t launch_eval_##suf(int, const KArgs&, int, size_t, hipStream_t);                 \
   hipError_t launch_fit_##suf(const FitArgs&, hipStream_t);                                  \
+  hipError_t launch_eval_layers_##suf(const KArgs&, const FitArgs&, size_t, hipStream_t);    \
   hipError_t launch_adam_pack_##suf(const AdamArgs&, hipStream_t);                           \
   hipError_t launch_pack_##suf(const double*, int, int, int, void*, void*, void*, void*, void*, \
                                void*, hipStream_t);
@@ -42,6 +43,14 @@ hipError_t launch_eval(int prec, int MT, const KArgs& a, int grid, size_t lds, h
     case BEST_FP32: return launch_eval_f32(MT, a, grid, lds, s);
     case BEST_FP16: return launch_eval_f16(MT, a, grid, lds, s);
     default: return launch_eval_bf16(MT, a, grid, lds, s);
+  }
+}
+hipError_t launch_eval_layers(int prec, const KArgs& k, const FitArgs& f, size_t lds, hipStream_t s) {
+  switch (prec) {
+    case BEST_FP32: return launch_eval_layers_f32(k, f, lds, s);
+    case BEST_FP16: return launch_eval_layers_f16(k, f, lds, s);
+    case BEST_BF16: return launch_eval_layers_bf16(k, f, lds, s);
+    default: return hipErrorInvalidValue;
   }
 }
 hipError_t launch_fit(int prec, const FitArgs& a, hipStream_t s) {
@@ -239,6 +248,52 @@ static KArgs base_args(const best_ctx* h) {
   return a;
 }
 
+// Largest batch evaluated layer by layer, every layer over the whole chip, instead of as tiles.  A
+// tile streams all weights through one CU, so a batch of few tiles costs a full round, 26 to 300 us,
+// whatever its size; the layers cost 2 nh kernels of 3 to 4 us until their work shows.  The lines are
+// where the two meet, network and type by network and type (log pi and gradient, us, tiles / layers;
+// values alone alike):
+//   BF16 256 x 4  64 points 22.6 / 28.5, never;  512 x 4  64 points 41.3 / 29.6, 1024 41.7 / 38.0,
+//   2048 41.9 / 48.9;  FP16 1024 x 5  64 points 187 / 57, 2048 168 / 114, 3072 168 / 148;
+//   1024 x 2  2048 points 51.9 / 40.2
+//   FP32 128 x 2  512 points 17.1 / 15.3;  256 x 4  2048 points 48.9 / 41.4;  512 x 4  64 points
+//   134 / 41, 2048 133 / 88, 3072 133 / 134;  1024 x 3  64 points 304 / 53, 2048 298 / 175
+static int64_t layer_points(const best_ctx* h) {
+  if (h->prec == BEST_FP64 || h->nh < 2 || h->tg.plain_mode == 2) return 0;
+  if (layout_for(h->prec, 1, h->H, h->d, h->nh, 0, 2).total > kLdsMax) return 0;
+  // activations and three panels, in the tiles' activation scratch
+  const int64_t have = (int64_t)h->grid_cap * h->hsave_stride * vasize(h->prec);
+  const int64_t per = (int64_t)h->H * (4 * h->nh + 3 * tsize(h->prec));
+  const int64_t most = h->prec == BEST_FP32 ? std::min(8 * h->H, 2048) : h->H >= 512 ? 2 * h->H : 0;
+  return std::min<int64_t>(most, have / per / 16 * 16);
+}
+
+// Points c0 .. c0 + n - 1 of the evaluation a, layer by layer.
+static int run_eval_layers(best_ctx* h, const KArgs& a, int64_t c0, int64_t n) {
+  KArgs k = a;
+  k.st.N = n;
+  k.ex_x += c0;
+  k.ex_lp += c0;
+  if (k.ex_g) k.ex_g += c0;
+  FitArgs f{};
+  f.mp = k.mp;
+  f.n = n;
+  f.ldb = (n + 15) / 16 * 16;
+  f.round_h = k.mp.lds_h;
+  k.mp.lds_h = 0;  // the closing kernel holds delta_1 alone
+  k.lds = layout_for(h->prec, 1, h->H, h->d, h->nh, 0, 2);
+  f.tg = k.tg;
+  f.x = k.ex_x;
+  f.x_pitch = k.ex_pitch;
+  f.act = (float*)h->hsave;
+  const size_t panel = (size_t)f.ldb * h->H * tsize(h->prec);
+  f.pp0 = f.act + (size_t)f.ldb * h->nh * h->H;
+  f.pp1 = (char*)f.pp0 + panel;
+  f.pp2 = (char*)f.pp1 + panel;
+  HIPCHK(h, launch_eval_layers(h->prec, k, f, k.lds.total, h->stream));
+  return BEST_OK;
+}
+
 static int run_eval(best_ctx* h, const double* X, int64_t pitch, int64_t n, double* LP,
                     double* G) {
   if (n <= 0) return BEST_OK;
@@ -288,6 +343,14 @@ static int run_eval(best_ctx* h, const double* X, int64_t pitch, int64_t n, doub
     }
   }
   const int64_t M = 16 * mt;
+  // the points of the last, partly filled round of tiles, or all of a small batch
+  const int64_t round = (int64_t)grid_cap * M, rem = n % round;
+  if (rem > 0 && rem <= layer_points(h)) {
+    if (int rc = run_eval_layers(h, a, n - rem, rem)) return rc;
+    n -= rem;
+    if (n == 0) return BEST_OK;
+    a.st.N = n;
+  }
   a.n_tiles = (n + M - 1) / M;
   const int grid = (int)std::min<int64_t>(a.n_tiles, grid_cap);
   HIPCHK(h, launch_eval(h->prec, mt, a, grid, lds, h->stream));
@@ -730,6 +793,7 @@ int best_logL_param_grad(best_ctx* h, const double* x, int64_t n, const double* 
   a.tg = h->tg;
   a.tg.mlp_coef = h->mlp_coef;
   a.x = x;
+  a.x_pitch = n;
   a.upstream = upstream;
   h->vj.fill(a, n);
   HIPCHK(h, launch_fit(h->prec, a, h->stream));

@@ -30,6 +30,7 @@ hipError_t launch_eval(int prec, int MT, const KArgs& a, int grid, size_t lds, h
 hipError_t launch_pack(int prec, const double* flat, int d, int H, int nh, void* wf, void* wb,
                        void* w1f, void* w1t, void* bias, void* wout, hipStream_t s);
 hipError_t launch_fit(int prec, const FitArgs& a, hipStream_t s);
+hipError_t launch_eval_layers(int prec, const KArgs& k, const FitArgs& f, size_t lds, hipStream_t s);
 hipError_t launch_adam_pack(int prec, const AdamArgs& a, hipStream_t s);
 
 // kernels_aux.hip

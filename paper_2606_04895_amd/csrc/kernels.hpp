@@ -613,6 +613,26 @@ struct IsWidePost<NoPost> {
   static constexpr bool value = true;
 };
 
+// No continuation, and a network already evaluated layer by layer: the tile's activations h_nh
+// (D-order FP32 blocks) and delta_1 (B fragments) in global memory.
+template <class T>
+struct PanelEval : NoPost {
+  const float* hL;
+  const T* d1;
+  const double* prec;  // the d x d precision matrix, and LDS for it
+  double* gp;
+  __device__ PanelEval(const float* h, const T* p, const double* m, double* q)
+      : hL(h), d1(p), prec(m), gp(q) {}
+};
+template <class T>
+struct IsPanelEval {
+  static constexpr bool value = false;
+};
+template <class T>
+struct IsPanelEval<PanelEval<T>> {
+  static constexpr bool value = true;
+};
+
 // ---------------------------------------------------------------------------------------
 // Wide lane groups for 8 < d <= 32 on 32-chain tiles (the width of the 1024-wide networks):
 // sixteen threads per chain, thread 16c + i holding components i and i + 16, sums over the
@@ -991,6 +1011,98 @@ __device__ __forceinline__ void gw_eval(const KArgs& a, const MlpSmem<P>& s, con
   post(c, i, valid, x, g, lp);
 }
 
+// Closing work of a layer-by-layer evaluation up to the FP64 assembly, for a 16-chain tile: the
+// in-box / in-training-box flags (sixteen threads per chain), the precision matrix copied to LDS (the
+// assembly reads d rows of it for every chain), and the network's output (with grad: its partial sums,
+// completed together with the input gradient) from the panels, in the order of mlp_forward and
+// mlp_backward.  One tile runs here per CU, so memory latency is all that counts: everything is
+// requested before anything is used, and each wave copies the k-steps of delta_1 that it multiplies
+// itself.
+template <class P>
+__device__ __forceinline__ void panel_close(const KArgs& a, const MlpSmem<P>& s, const TView& X, int mv,
+                                            int* inbox, int* intrain,
+                                            const PanelEval<typename P::T>& pe, bool grad) {
+  using T = typename P::T;
+  using frag = typename P::frag;
+  const Target& tg = a.tg;
+  const MlpParams& mp = a.mp;
+  const int tid = local_tid(), lane = tid & 63, g = lane >> 4, wv = tid >> 6, cl = lane & 15;
+  const int RTW = mp.H / (16 * kWaves), KS = mp.H / P::KSTEP, d = tg.d, dd = d * d;
+  const float* __restrict__ Wo = (const float*)mp.wout;
+  const f32x4* __restrict__ h4 = (const f32x4*)pe.hL + wv * RTW * 64 + lane;
+  const frag* __restrict__ src = (const frag*)pe.d1 + lane;
+  frag* dst = (frag*)((((mp.nh - 1) & 1) == 0) ? s.dlt0 : s.dlt1) + lane;
+  constexpr int U = 4;
+  f32x4 h[U], wo[U];
+  frag dl[U];
+  double pr[4], x[2], lo[2], hi[2];
+  const int c = (tid >> 4) & 15, i = tid & 15, cc = clampd(c, mv);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    h[u] = h4[clampd(u, RTW) * 64];
+    wo[u] = *(const f32x4*)(Wo + (wv * RTW + clampd(u, RTW)) * 16 + 4 * g);
+    dl[u] = src[clampd(wv + u * kWaves, KS) * 64];
+    pr[u] = pe.prec[clampd(tid + u * kThreads, dd)];
+  }
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int kk = clampd(i + 16 * u, d);
+    x[u] = X(kk, cc);
+    lo[u] = tg.lower[kk];
+    hi[u] = tg.upper[kk];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  float po = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (u < RTW)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) po += wo[u][r] * h[u][r];
+  for (int rr = U; rr < RTW; ++rr) {
+    const f32x4 w = *(const f32x4*)(Wo + (wv * RTW + rr) * 16 + 4 * g), hv = h4[rr * 64];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) po += w[r] * hv[r];
+  }
+  const float v = sum_lane_groups(po);
+  if (g == 0) s.outp[wv * 16 + cl] = v;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if (wv + u * kWaves < KS) dst[(wv + u * kWaves) * 64] = dl[u];
+    if (tid + u * kThreads < dd) pe.gp[tid + u * kThreads] = pr[u];
+  }
+  for (int ks = wv + U * kWaves; ks < KS; ks += kWaves) dst[ks * 64] = src[ks * 64];
+  if (tid < 256) {
+    int ib = 1, it = 1;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int k = i + 16 * u, kk = clampd(k, d);
+      const bool act = c < mv && k < d;
+      if (act) ib &= (x[u] >= lo[u]) & (x[u] <= hi[u]);
+      if (tg.plain_mode == 1) {
+        const double tlo = tg.train_lo[kk], thi = tg.train_hi[kk];
+        if (act) it &= (x[u] >= tlo) & (x[u] <= thi);
+      }
+    }
+    ib = gw_and<16>(ib);
+    it = gw_and<16>(it);
+    if (i == 0) {
+      inbox[c] = ib;
+      intrain[c] = it;
+    }
+  }
+  if (grad) {
+    mlp_input_grad<P, 1>(mp, s, (const T*)(dst - lane));
+    return;
+  }
+  __syncthreads();
+  if (tid < 16) {
+    float o = s.outp[tid];
+    for (int w = 1; w < kWaves; ++w) o += s.outp[w * 16 + tid];
+    s.out[tid] = o + Wo[mp.H];
+  }
+  __syncthreads();
+}
+
 // Target evaluation for a tile.  staged: the caller wrote the emulator inputs and flags
 // (grp_stage).  On the lane-group path, post(c, i, valid, x_i, g_i, log pi) runs in every
 // thread of the tile's chains after log pi and its gradient are written (x_i and g_i this
@@ -1017,7 +1129,7 @@ __device__ __forceinline__ void eval_tile(const KArgs& a, char* smem, typename P
   int* intrain = inbox + M;
 
   // normalised inputs t = (x - center) * invscale; padding chains and components are 0
-  if (!staged) {
+  if (!IsPanelEval<Post>::value && !staged) {
     const int K1 = a.mp.ks1 * IP::KSTEP;
     for (int e = tid; e < M * K1; e += kThreads) {
       const int c = e / K1, i = e % K1;
@@ -1054,7 +1166,9 @@ __device__ __forceinline__ void eval_tile(const KArgs& a, char* smem, typename P
   }
 
   // the input layer joins the barrier that publishes the inputs and flags
-  if (tg.plain_mode != 2) {
+  if constexpr (IsPanelEval<Post>::value) {
+    panel_close<P>(a, s, X, mv, inbox, intrain, post, grad);
+  } else if (tg.plain_mode != 2) {
     mlp_forward<P, MT>(a.mp, s, hsave, grad, true, grad);
     if (grad) mlp_backward<P, MT>(a.mp, s, hsave);
   } else {

@@ -480,6 +480,80 @@ __device__ __forceinline__ void mlp_forward(const MlpParams& mp, const MlpSmem<P
   __syncthreads();
 }
 
+// Closing part of the backward pass, from delta_1 (d1, B fragments) and the forward pass's output
+// partials: writes s.gth[c][i] = d out / d t_i and completes s.out.  Its first barrier publishes
+// both; ends with a barrier.
+template <class P, int MT>
+__device__ __forceinline__ void mlp_input_grad(const MlpParams& mp, const MlpSmem<P>& s,
+                                               const typename P::T* d1) {
+  using acc = typename P::acc;
+  using vec = typename P::vec;
+  using accv = typename P::accv;
+  using frag = typename P::frag;
+  constexpr int M = 16 * MT;
+  const int tid = local_tid(), lane = tid & 63, g = lane >> 4, wv = tid >> 6, cl = lane & 15;
+  const int d = mp.d, KS = mp.H / P::KSTEP;
+  const acc* __restrict__ Wo = (const acc*)mp.wout;
+  // ---- d out / d t = W_1^T delta_1: the K = H k-steps are dealt to the waves round-robin
+  // (wave w takes w, w + 8, ...) and the 8 partial tiles are summed in wave order; the
+  // first row tile's leading fragments are loaded before the barrier ----
+  // per-wave partial sums (the layout places them in the delta buffer that does not hold
+  // delta_1 when they fit there)
+  acc* red = s.red;
+  {
+    const frag* __restrict__ Af = (const frag*)mp.w1t + lane;
+    const frag* __restrict__ Bf = (const frag*)d1 + lane;
+    constexpr int PF = 4;
+    frag a0[PF];
+#pragma unroll
+    for (int q = 0; q < PF; ++q) {
+      const int ks = wv + q * kWaves;
+      if (ks < KS) a0[q] = Af[(int64_t)ks * 64];
+    }
+    __syncthreads();
+    for (int rt = 0; rt < mp.rti; ++rt) {
+      accv part[MT];
+#pragma unroll
+      for (int ct = 0; ct < MT; ++ct) part[ct] = accv{};
+      int ks = wv;
+      if (rt == 0) {
+#pragma unroll
+        for (int q = 0; q < PF; ++q, ks += kWaves) {
+          if (ks < KS) {
+#pragma unroll
+            for (int ct = 0; ct < MT; ++ct)
+              part[ct] = P::mma(a0[q], Bf[(ct * KS + ks) * 64], part[ct]);
+          }
+        }
+      }
+      for (; ks < KS; ks += kWaves) {
+        const frag a = Af[((int64_t)rt * KS + ks) * 64];
+#pragma unroll
+        for (int ct = 0; ct < MT; ++ct) part[ct] = P::mma(a, Bf[(ct * KS + ks) * 64], part[ct]);
+      }
+#pragma unroll
+      for (int ct = 0; ct < MT; ++ct)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int i = rt * 16 + P::drow(g, r);
+          if (i < d) red[(wv * M + ct * 16 + cl) * d + i] = (acc)part[ct][r];
+        }
+    }
+  }
+  __syncthreads();
+  for (int e = tid; e < M * d; e += kThreads) {
+    acc v = red[e];
+    for (int w = 1; w < kWaves; ++w) v += red[w * M * d + e];
+    s.gth[e] = (vec)v;
+  }
+  if (tid < M) {
+    acc o = s.outp[tid];
+    for (int w = 1; w < kWaves; ++w) o += s.outp[w * M + tid];
+    s.out[tid] = o + Wo[mp.H];
+  }
+  __syncthreads();
+}
+
 // Backward pass (reverse mode, upstream 1) after a forward pass that fused delta_L (networks of
 // more than one hidden layer) and deferred the output: writes s.gth[c][i] = d out / d t_i and
 // completes s.out from the forward's partials.  Ends with a barrier.
@@ -488,12 +562,10 @@ __device__ __forceinline__ void mlp_backward(const MlpParams& mp, const MlpSmem<
                                              typename P::acc* __restrict__ hsave) {
   using T = typename P::T;
   using acc = typename P::acc;
-  using vec = typename P::vec;
   using accv = typename P::accv;
-  using frag = typename P::frag;
   constexpr int M = 16 * MT;
   const int tid = local_tid(), lane = tid & 63, g = lane >> 4, wv = tid >> 6, cl = lane & 15;
-  const int d = mp.d, H = mp.H, nh = mp.nh;
+  const int H = mp.H, nh = mp.nh;
   const int KS = H / P::KSTEP, RTW = H / (16 * kWaves);
   const acc* __restrict__ Wo = (const acc*)mp.wout;
 
@@ -543,66 +615,8 @@ __device__ __forceinline__ void mlp_backward(const MlpParams& mp, const MlpSmem<
     gemm_pass<P, MT>(nh - 1, KS, wv * RTW, RTW, Aof, Bof, pre, epi);
   }
 
-  // ---- d out / d t = W_1^T delta_1: the K = H k-steps are dealt to the waves round-robin
-  // (wave w takes w, w + 8, ...) and the 8 partial tiles are summed in wave order; the
-  // first row tile's leading fragments are loaded before the barrier ----
-  // per-wave partial sums (the layout places them in the delta buffer that does not hold
-  // delta_1 when they fit there)
-  acc* red = s.red;
-  {
-    // delta_1 is the output of the last hidden-layer step above, or delta_L if nh == 1
-    const T* d1 = (((nh - 1) & 1) == 0) ? s.dlt0 : s.dlt1;
-    const frag* __restrict__ Af = (const frag*)mp.w1t + lane;
-    const frag* __restrict__ Bf = (const frag*)d1 + lane;
-    constexpr int PF = 4;
-    frag a0[PF];
-#pragma unroll
-    for (int q = 0; q < PF; ++q) {
-      const int ks = wv + q * kWaves;
-      if (ks < KS) a0[q] = Af[(int64_t)ks * 64];
-    }
-    __syncthreads();
-    for (int rt = 0; rt < mp.rti; ++rt) {
-      accv part[MT];
-#pragma unroll
-      for (int ct = 0; ct < MT; ++ct) part[ct] = accv{};
-      int ks = wv;
-      if (rt == 0) {
-#pragma unroll
-        for (int q = 0; q < PF; ++q, ks += kWaves) {
-          if (ks < KS) {
-#pragma unroll
-            for (int ct = 0; ct < MT; ++ct)
-              part[ct] = P::mma(a0[q], Bf[(ct * KS + ks) * 64], part[ct]);
-          }
-        }
-      }
-      for (; ks < KS; ks += kWaves) {
-        const frag a = Af[((int64_t)rt * KS + ks) * 64];
-#pragma unroll
-        for (int ct = 0; ct < MT; ++ct) part[ct] = P::mma(a, Bf[(ct * KS + ks) * 64], part[ct]);
-      }
-#pragma unroll
-      for (int ct = 0; ct < MT; ++ct)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = rt * 16 + P::drow(g, r);
-          if (i < d) red[(wv * M + ct * 16 + cl) * d + i] = (acc)part[ct][r];
-        }
-    }
-  }
-  __syncthreads();
-  for (int e = tid; e < M * d; e += kThreads) {
-    acc v = red[e];
-    for (int w = 1; w < kWaves; ++w) v += red[w * M * d + e];
-    s.gth[e] = (vec)v;
-  }
-  if (tid < M) {
-    acc o = s.outp[tid];
-    for (int w = 1; w < kWaves; ++w) o += s.outp[w * M + tid];
-    s.out[tid] = o + Wo[H];
-  }
-  __syncthreads();
+  // delta_1 is the output of the last hidden-layer step above, or delta_L if nh == 1
+  mlp_input_grad<P, MT>(mp, s, (((nh - 1) & 1) == 0) ? s.dlt0 : s.dlt1);
 }
 
 }  // namespace best

@@ -222,9 +222,10 @@ struct FitArgs {
   // for points whose log pi does not use the network
   Target tg;
   const double *x, *upstream;
+  int64_t x_pitch;
   float *act, *hx;  // [nh] blocks
   float *th, *up;   // [d][ldb], [ldb]
-  void *pp0, *pp1;
+  void *pp0, *pp1, *pp2;  // pp2: delta_{nh-1} of an evaluation, written while pp0 may be read
 };
 
 // Launch index -> tile index such that the blocks of one XCD (index mod 8) own a contiguous run
@@ -279,8 +280,10 @@ __device__ __forceinline__ void panel_store(const FitArgs& a, typename P::T* pan
 }
 
 // Input layer, kInRows row tiles of one column tile per wave (bound by latency: d <= 32).
+// EVAL: for the evaluation of points, which needs no inputs or activations in the weight gradients'
+// order.
 constexpr int kInRows = 2;
-template <class P>
+template <class P, bool EVAL>
 __global__ __launch_bounds__(256) void fit_input_kernel(FitArgs a) {
   using IP = Prec<float>;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane >> 4, cl = lane & 15;
@@ -298,9 +301,9 @@ __global__ __launch_bounds__(256) void fit_input_kernel(FitArgs a) {
       float v = 0.f;
       if (valid && i < d)
         v = a.t_in ? a.t_in[src * d + i]
-                   : (float)((a.x[i * a.n + c] - a.tg.in_center[i]) * a.tg.in_invscale[i]);
+                   : (float)((a.x[i * a.x_pitch + c] - a.tg.in_center[i]) * a.tg.in_invscale[i]);
       b[ks][r] = v;
-      if (lead && i < d) a.th[(int64_t)i * a.ldb + c] = v;
+      if (!EVAL && lead && i < d) a.th[(int64_t)i * a.ldb + c] = v;
     }
   const f32x4* __restrict__ W = (const f32x4*)a.mp.w1f + lane;
   const float* __restrict__ bias = (const float*)a.mp.bias;
@@ -317,7 +320,7 @@ __global__ __launch_bounds__(256) void fit_input_kernel(FitArgs a) {
     for (int r = 0; r < 4; ++r) h[r] = act_tanh(v[r] + bi[r]);
     const int64_t o = fit_block(a, 0, ct, rt);
     ((f32x4*)a.act)[o + lane] = h;
-    ((f32x4*)a.hx)[o + dw_slot(lane)] = quad_transpose(h, lane);
+    if constexpr (!EVAL) ((f32x4*)a.hx)[o + dw_slot(lane)] = quad_transpose(h, lane);
     if constexpr (sizeof(typename P::T) == 2)
       panel_store<P>(a, (typename P::T*)a.pp0, ct, rt, lane, h);
   }
@@ -328,8 +331,10 @@ __global__ __launch_bounds__(256) void fit_input_kernel(FitArgs a) {
 // weights (1 KiB contiguous per fragment) and the panel fragments of the next kFitRing k-steps
 // are in flight.  With C = 2 and R = 1 (the 1024-wave split of 1024 points) a wave loads
 // 3 KiB per 256 FP32 MFMA cycles, 48 B per clock and CU with the panel shared through L1.
+// EVAL (points, upstream 1): the last forward layer also writes delta_{nh-1} = w_out (1 - h^2), and
+// every reverse layer only its panel.
 constexpr int kFitRing = 4;
-template <class P, int R, int C, bool BWD>
+template <class P, int R, int C, bool BWD, bool EVAL>
 __global__ __launch_bounds__(256) void fit_layer_kernel(FitArgs a, int l) {
   using T = typename P::T;
   using frag = typename P::frag;
@@ -343,7 +348,7 @@ __global__ __launch_bounds__(256) void fit_layer_kernel(FitArgs a, int l) {
   const frag* __restrict__ A = (const frag*)Aw + (int64_t)rt0 * KS * 64 + lane;
   const int par = (a.mp.nh - 1 - l) & 1;  // reverse pass: delta_{nh-1} is in pp0
   const T* Bin;
-  if constexpr (BWD) Bin = (const T*)(par ? a.pp1 : a.pp0);
+  if constexpr (BWD) Bin = (const T*)(EVAL && l == a.mp.nh - 1 ? a.pp2 : par ? a.pp1 : a.pp0);
   else if constexpr (sizeof(T) == 4) Bin = (const T*)a.act + (l - 1) * CT * 16 * H;
   else Bin = (const T*)((l & 1) ? a.pp0 : a.pp1);
   const frag* __restrict__ B[C];
@@ -373,6 +378,13 @@ __global__ __launch_bounds__(256) void fit_layer_kernel(FitArgs a, int l) {
     } else {
       e[i][0] = *(const f32x4*)((const float*)a.mp.bias + (int64_t)l * H + (rt0 + i) * 16 + 4 * g);
     }
+  }
+  const bool last = EVAL && !BWD && l == a.mp.nh - 1;
+  f32x4 wo[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    if constexpr (EVAL && !BWD)
+      if (last) wo[i] = *(const f32x4*)((const float*)a.mp.wout + (rt0 + i) * 16 + 4 * g);
   }
   f32x4 acc[R][C] = {};
   auto mma = [&](int p) {
@@ -409,17 +421,45 @@ __global__ __launch_bounds__(256) void fit_layer_kernel(FitArgs a, int l) {
       }
       const int64_t ct = ct0 + j;
       if constexpr (BWD) {
-        if (l > 1) panel_store<P>(a, (T*)(par ? a.pp0 : a.pp1), ct, rt0 + i, lane, v);
-        ((f32x4*)a.act)[fit_block(a, l - 1, ct, rt0 + i) + dw_slot(lane)] = quad_transpose(v, lane);
+        if (EVAL || l > 1) panel_store<P>(a, (T*)(par ? a.pp0 : a.pp1), ct, rt0 + i, lane, v);
+        if constexpr (!EVAL)
+          ((f32x4*)a.act)[fit_block(a, l - 1, ct, rt0 + i) + dw_slot(lane)] = quad_transpose(v, lane);
       } else {
         const int64_t o = fit_block(a, l, ct, rt0 + i);
         ((f32x4*)a.act)[o + lane] = v;
-        ((f32x4*)a.hx)[o + dw_slot(lane)] = quad_transpose(v, lane);
+        if constexpr (!EVAL) ((f32x4*)a.hx)[o + dw_slot(lane)] = quad_transpose(v, lane);
+        if (last) {
+          f32x4 dl;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) dl[r] = wo[i][r] * (1.0f - v[r] * v[r]);
+          panel_store<P>(a, (T*)a.pp2, ct, rt0 + i, lane, dl);
+        }
         if constexpr (sizeof(T) == 2) {
           if (l + 1 < a.mp.nh) panel_store<P>(a, (T*)((l & 1) ? a.pp1 : a.pp0), ct, rt0 + i, lane, v);
         }
       }
     }
+}
+
+// Closing kernel of a layer-by-layer evaluation: one column tile per workgroup takes the network's
+// output from h_{nh-1}, d out / d t from delta_0 and assembles log pi and its gradient, in the
+// tile engine's order throughout.  Bound by latency, like the layers of a small batch (64 points of
+// 12 -> 512 x 4: 7 us here, 3.5 us a layer; one tile per CU through all weights took 41 us, the eight
+// kernels take 30).
+template <class P>
+__global__ __launch_bounds__(kThreads) void eval_close_kernel(KArgs a, FitArgs f) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  using T = typename P::T;
+  const int64_t ct = blockIdx.x, c0 = ct * 16;
+  const int mv = (int)((a.st.N - c0) < 16 ? (a.st.N - c0) : 16);
+  const int nh = a.mp.nh;
+  const T* d0 = (const T*)(((nh - 2) & 1) ? f.pp0 : f.pp1) + ct * 16 * a.mp.H;
+  const PanelEval<T> pe{f.act + fit_block(f, nh - 1, ct, 0) * 4, d0,
+                        a.tg.gprec, generic_ptr((double*)(smem + a.lds.cst))};
+  a.tg.gprec = pe.gp;
+  eval_tile<P, 1>(a, smem, nullptr, TView{const_cast<double*>(a.ex_x) + c0, a.ex_pitch}, mv,
+                  a.ex_lp + c0, TView{a.ex_g ? a.ex_g + c0 : nullptr, a.ex_pitch},
+                  a.ex_grad != 0, true, false, pe);
 }
 
 // Network output, upstream gradient (training: 2 (out - y) / n and the loss; target points: the
