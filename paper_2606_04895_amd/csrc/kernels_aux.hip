@@ -1,6 +1,6 @@
 // Non-templated kernels: walker initialisation, re-whitening, dual averaging, statistics,
-// ensemble moments + jittered Cholesky (Sec. 3.2), multi-chain autocovariances for ESS,
-// Adam, and the training weight-gradient GEMMs.
+// ensemble moments + jittered Cholesky (Sec. 3.2), multi-chain autocovariances for ESS, the plain
+// model's values, and the training weight-gradient GEMMs.
 #include <mutex>
 #include <type_traits>
 

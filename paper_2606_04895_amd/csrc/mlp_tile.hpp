@@ -260,7 +260,8 @@ __device__ __forceinline__ void gemm_in(const typename IP::T* __restrict__ A, in
     for (int ct = 0; ct < MT; ++ct) epi(rt0 + rr, ct, c[rr][ct], pv[rr]);
 }
 
-// Input layer over this wave's RTW row tiles: eight at once when the input fits one k-step.
+// Input layer over this wave's RTW row tiles: eight at once when the input fits one k-step, else four
+// or two where they divide the tiles, else one by one.
 template <class IP, int MT, class Pre, class Epi>
 __device__ __forceinline__ void gemm_in_rows(const typename IP::T* A, int KS,
                                              const typename IP::T* Bl, int rtw0, int RTW,
@@ -271,10 +272,11 @@ __device__ __forceinline__ void gemm_in_rows(const typename IP::T* A, int KS,
   } else if (RTW % 4 == 0) {
     for (int r = 0; r < RTW; r += 4)
       gemm_in<IP, 4, MT, kMaxKs1>(A, KS, Bl, rtw0 + r, pre, epi, sync && r == 0);
-  } else if (RTW % 2 == 0) {
+  } else if (RTW == 2) {
     gemm_in<IP, 2, MT, kMaxKs1>(A, KS, Bl, rtw0, pre, epi, sync);
   } else {
-    gemm_in<IP, 1, MT, kMaxKs1>(A, KS, Bl, rtw0, pre, epi, sync);
+    for (int r = 0; r < RTW; ++r)
+      gemm_in<IP, 1, MT, kMaxKs1>(A, KS, Bl, rtw0 + r, pre, epi, sync && r == 0);
   }
 }
 
