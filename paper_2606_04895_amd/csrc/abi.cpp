@@ -537,15 +537,17 @@ static int upload_problem(best_ctx* h, const best_problem* p) {
     HIPCHK(h, m.upload((double**)&t.pg0, pm->gamma0, nt, s));
     HIPCHK(h, m.upload((double**)&t.pc, pm->center, d, s));
     HIPCHK(h, m.upload((double**)&t.pis, pm->invscale, d, s));
-    // tables of the recurrence over the bins (see plain_wave).  The grid counts as even where no
-    // point is further from x_0 + j h than rounding puts it (two ulps of the largest)
+    // tables of the recurrence over the bins (see plain_wave).  The grid counts as even where every
+    // point is finite and none further from x_0 + j h than rounding puts it (two ulps of the largest)
     double xm = 0, off = 0;
+    bool finite = true;
     const double x0 = pm->xgrid[0], hx = nb > 1 ? (pm->xgrid[nb - 1] - x0) / (double)(nb - 1) : 0.0;
     for (size_t j = 0; j < nb; ++j) {
+      finite = finite && std::isfinite(pm->xgrid[j]);
       xm = std::max(xm, std::fabs(pm->xgrid[j]));
       off = std::max(off, std::fabs(pm->xgrid[j] - (x0 + (double)j * hx)));
     }
-    t.pl_even = off <= xm * 0x1p-51 ? 1 : 0;
+    t.pl_even = finite && off <= xm * 0x1p-51 ? 1 : 0;
     t.pl_step = 64.0 * hx;
     auto turn = [](double k, double x, double* out) {  // cos, sin of 2 pi k x
       long double f = (long double)k * x;

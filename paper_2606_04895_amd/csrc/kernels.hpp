@@ -21,7 +21,7 @@ struct Target {
   const double *train_lo, *train_hi;
   int n_bins, n_terms;
   const double *xgrid, *data, *w2, *pa, *pg, *pp, *pk, *pg0, *pc, *pis;
-  int pl_even;            // the grid is evenly spaced: the recurrence of plain_wave applies
+  int pl_even;            // the grid is finite and evenly spaced: the recurrence of plain_wave applies
   double pl_step;         // 64 grid spacings
   const double* pl_rot;   // [n_terms][2] cos, sin of 2 pi k over pl_step
   const f64x2* pl_trig;   // [segments][kMaxTerms][64] cos, sin of 2 pi k x at a segment's first bins
@@ -337,17 +337,25 @@ __device__ __forceinline__ double lane_value(double v, int m) {
 }
 
 // Plain spectrum log-likelihood of one chain by one wave, without the gradient (training data,
-// importance weights, MH and the ensemble moves); lane l takes bins l, l + 64, ...  Term m's amplitude times its damped oscillation, as a complex number
+// importance weights, MH and the ensemble moves); lane l takes bins l, l + 64, ...  Term m's
+// amplitude times its damped oscillation, as a complex number
 //   w_m(j) = a_m exp(-gamma_m x_j) exp(i (2 pi k_m x_j + phi_m)),
 // advances over an evenly spaced grid by one complex factor z_m per 64 bins, so a bin costs
 // four FP64 multiply-adds per term instead of an exponential and a sine and cosine.  Each lane
 // starts from its first bin (exp(-gamma x), and the chain-independent cos / sin(2 pi k x) from a
-// table) and restarts from the bin itself every kPlainSeg steps, so that rounding grows over at
-// most that many factors: below the rounding of the phase 2 pi k x + phi itself (half an ulp of 150
-// rad at k = 24).  Bound by the FP64 rate: 20000 points, 2500 bins x 8 terms 318 us in the tile
-// kernels (plain_eval_kernel: 121 us), against 3550 us with exp and sincos per bin and a workgroup
-// per chain.  A grid that is not evenly spaced evaluates every bin directly.
+// table) and restarts from the bin itself every kPlainSeg steps.  Bound by the FP64 rate: 20000
+// points, 2500 bins x 8 terms 318 us in the tile kernels (plain_eval_kernel: 121 us), against 3550 us
+// with exp and sincos per bin and a workgroup per chain.
+//
+// The recurrence holds where no factor of a term leaves the range of FP64 anywhere on the grid: a
+// seed that underflows would leave a term that grows along the grid (a descending grid, a negative
+// damping) at zero, one that overflows would turn a decaying term into NaN.  -gamma x is largest and
+// smallest at the ends of the grid, so |ln a| and |gamma x| there at most kPlainExp bound every
+// product by exp(+-2 kPlainExp).  A chain with a term outside (NaN included), and every chain on a
+// grid that is not evenly spaced or not finite, is evaluated bin by bin with the expressions of
+// plain_chain.
 constexpr int kPlainSeg = 64;
+constexpr double kPlainExp = 300.0;
 __device__ __forceinline__ void plain_wave(const Target& tg, const TView& X, int c, double* outv) {
   constexpr double kPi = 3.141592653589793;
   const int lane = local_tid() & 63, d = tg.d, nt = tg.n_terms, nb = tg.n_bins;
@@ -363,55 +371,45 @@ __device__ __forceinline__ void plain_wave(const Target& tg, const TView& X, int
   }
   const bool own = lane < nt;
   const double th = tanh(sp), A = own ? exp(sa) : 0.0, gm = own ? tg.pg0[lm] * exp(sg) : 0.0;
-  double sph, cph;
-  sincos(kPi * th, &sph, &cph);
-  const double ez = own ? exp(-gm * tg.pl_step) : 0.0;
-  const double Pl = A * cph, Ql = A * sph, zrl = ez * tg.pl_rot[2 * lm], zil = ez * tg.pl_rot[2 * lm + 1];
-  double P[kMaxTerms], Q[kMaxTerms], ga[kMaxTerms], zr[kMaxTerms], zi[kMaxTerms];
-#pragma unroll
-  for (int m = 0; m < kMaxTerms; ++m) {
-    P[m] = lane_value(Pl, m);
-    Q[m] = lane_value(Ql, m);
-    ga[m] = lane_value(gm, m);
-    zr[m] = lane_value(zrl, m);
-    zi[m] = lane_value(zil, m);
-  }
-  double ll = 0, re[kMaxTerms], im[kMaxTerms];
-  // terms past n_terms have P = Q = z = 0 and stay zero
-  auto seed = [&](int j, bool table) {
-    const double x = tg.xgrid[j];
+  const bool in = fabs(sa) <= kPlainExp && fabs(gm * tg.xgrid[0]) <= kPlainExp &&
+                  fabs(gm * tg.xgrid[nb - 1]) <= kPlainExp;
+  double ll = 0;
+  if (tg.pl_even && __ballot(own && !in) == 0) {
+    double sph, cph;
+    sincos(kPi * th, &sph, &cph);
+    const double ez = own ? exp(-gm * tg.pl_step) : 0.0;
+    const double Pl = A * cph, Ql = A * sph, zrl = ez * tg.pl_rot[2 * lm], zil = ez * tg.pl_rot[2 * lm + 1];
+    double P[kMaxTerms], Q[kMaxTerms], ga[kMaxTerms], zr[kMaxTerms], zi[kMaxTerms];
 #pragma unroll
     for (int m = 0; m < kMaxTerms; ++m) {
-      double cs, sn;
-      if (table) {
-        const f64x2 t = tg.pl_trig[((int64_t)(j / (64 * kPlainSeg)) * kMaxTerms + m) * 64 + (j & 63)];
-        cs = t[0];
-        sn = t[1];
-      } else {
-        sincos(2.0 * kPi * tg.pk[m < nt ? m : nt - 1] * x, &sn, &cs);
-      }
-      const double e = exp(-ga[m] * x);
-      re[m] = e * (cs * P[m] - sn * Q[m]);
-      im[m] = e * (sn * P[m] + cs * Q[m]);
+      P[m] = lane_value(Pl, m);
+      Q[m] = lane_value(Ql, m);
+      ga[m] = lane_value(gm, m);
+      zr[m] = lane_value(zrl, m);
+      zi[m] = lane_value(zil, m);
     }
-  };
-  auto bin = [&](int j, bool valid, double dat, double w2) {
-    double spec = 0;
-#pragma unroll
-    for (int m = 0; m < kMaxTerms; ++m) spec += re[m];
-    const double dr = valid ? spec - dat : 0.0, r = dr * w2;
-    ll += dr * r;
-  };
-  if (tg.pl_even) {
+    double re[kMaxTerms], im[kMaxTerms];
     for (int j0 = 0; j0 < nb; j0 += 64 * kPlainSeg) {
-      seed(j0 + lane < nb ? j0 + lane : nb - 1, true);
+      const int js = j0 + lane < nb ? j0 + lane : nb - 1;
+      const double x = tg.xgrid[js];
+      // terms past n_terms have P = Q = z = 0 and stay zero
+#pragma unroll
+      for (int m = 0; m < kMaxTerms; ++m) {
+        const f64x2 t = tg.pl_trig[((int64_t)(js / (64 * kPlainSeg)) * kMaxTerms + m) * 64 + (js & 63)];
+        const double e = exp(-ga[m] * x);
+        re[m] = e * (t[0] * P[m] - t[1] * Q[m]);
+        im[m] = e * (t[1] * P[m] + t[0] * Q[m]);
+      }
       const int j1 = j0 + 64 * kPlainSeg < nb ? j0 + 64 * kPlainSeg : nb;
-      double dat = tg.data[j0 + lane < nb ? j0 + lane : nb - 1];
-      double w2 = tg.w2[j0 + lane < nb ? j0 + lane : nb - 1];
+      double dat = tg.data[js], w2 = tg.w2[js];
       for (int jb = j0; jb < j1; jb += 64) {
         const int j = jb + lane, jn = j + 64 < nb ? j + 64 : nb - 1;
         const double dn = tg.data[jn], wn = tg.w2[jn];
-        bin(j, j < nb, dat, w2);
+        double spec = 0;
+#pragma unroll
+        for (int m = 0; m < kMaxTerms; ++m) spec += re[m];
+        const double dr = j < nb ? spec - dat : 0.0;
+        ll += dr * (dr * w2);
         dat = dn;
         w2 = wn;
 #pragma unroll
@@ -425,8 +423,16 @@ __device__ __forceinline__ void plain_wave(const Target& tg, const TView& X, int
   } else {
     for (int jb = 0; jb < nb; jb += 64) {
       const int j = jb + lane, jj = j < nb ? j : nb - 1;
-      seed(jj, false);
-      bin(j, j < nb, tg.data[jj], tg.w2[jj]);
+      const double x = tg.xgrid[jj];
+      double spec = 0;
+      for (int m = 0; m < nt; ++m) {
+        const double e = exp(-lane_value(gm, m) * x);
+        double sn, cs;
+        sincos(2.0 * kPi * tg.pk[m] * x + kPi * lane_value(th, m), &sn, &cs);
+        spec += lane_value(A, m) * (e * cs);
+      }
+      const double dr = j < nb ? spec - tg.data[jj] : 0.0;
+      ll += dr * (dr * tg.w2[jj]);
     }
   }
   ll = wave_sum(ll);
