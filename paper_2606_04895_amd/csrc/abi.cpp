@@ -305,7 +305,7 @@ static int run_eval(best_ctx* h, const double* X, int64_t pitch, int64_t n, doub
   a.ex_g = G;
   a.ex_grad = G != nullptr;
   if (a.tg.plain_mode == 2 && !G) {
-    HIPCHK(h, launch_plain_eval(a, h->stream));
+    HIPCHK(h, launch_plain_eval(a, h->n_cu, h->stream));
     return BEST_OK;
   }
   int mt = h->MT, grid_cap = h->grid_cap;
@@ -537,35 +537,22 @@ static int upload_problem(best_ctx* h, const best_problem* p) {
     HIPCHK(h, m.upload((double**)&t.pg0, pm->gamma0, nt, s));
     HIPCHK(h, m.upload((double**)&t.pc, pm->center, d, s));
     HIPCHK(h, m.upload((double**)&t.pis, pm->invscale, d, s));
-    // tables of the recurrence over the bins (see plain_wave).  The grid counts as even where every
-    // point is finite and none further from x_0 + j h than rounding puts it (two ulps of the largest)
+    // the recurrence over the bins (see plain_wave).  The grid counts as even where every point is
+    // finite and none further from x_0 + j h than rounding puts it (two ulps of the largest)
     double xm = 0, off = 0;
-    bool finite = true;
+    bool finite = nb <= kPlainTable;
     const double x0 = pm->xgrid[0], hx = nb > 1 ? (pm->xgrid[nb - 1] - x0) / (double)(nb - 1) : 0.0;
-    for (size_t j = 0; j < nb; ++j) {
-      finite = finite && std::isfinite(pm->xgrid[j]);
+    for (size_t j = 0; j < nb && finite; ++j) {
+      finite = std::isfinite(pm->xgrid[j]);
       xm = std::max(xm, std::fabs(pm->xgrid[j]));
       off = std::max(off, std::fabs(pm->xgrid[j] - (x0 + (double)j * hx)));
     }
     t.pl_even = finite && off <= xm * 0x1p-51 ? 1 : 0;
     t.pl_step = 64.0 * hx;
-    auto turn = [](double k, double x, double* out) {  // cos, sin of 2 pi k x
-      long double f = (long double)k * x;
-      f = 2.0L * 3.141592653589793238462643383279503L * (f - roundl(f));
-      out[0] = (double)cosl(f);
-      out[1] = (double)sinl(f);
-    };
-    const size_t seg = 64 * kPlainSeg, n_seg = (nb + seg - 1) / seg;
-    std::vector<double> rot(2 * nt), trig(n_seg * kMaxTerms * 64 * 2, 0.0);
-    for (size_t q = 0; q < nt; ++q) {
-      turn(pm->k[q], t.pl_step, &rot[2 * q]);
-      for (size_t g = 0; g < n_seg; ++g)
-        for (size_t l = 0; l < 64 && g * seg + l < nb; ++l)
-          turn(pm->k[q], pm->xgrid[g * seg + l], &trig[((g * kMaxTerms + q) * 64 + l) * 2]);
+    if (t.pl_even) {
+      HIPCHK(h, m.alloc((f64x2**)&t.pl_tab, (nb + 63) / 64 * 64 * (nt + 1)));
+      HIPCHK(h, launch_plain_table(t, (f64x2*)t.pl_tab, s));
     }
-    HIPCHK(h, m.upload((double**)&t.pl_rot, rot.data(), rot.size(), s));
-    HIPCHK(h, m.upload((double**)&t.pl_trig, trig.data(), trig.size(), s));
-    HIPCHK(h, hipStreamSynchronize(s));  // the tables are local
   }
   h->lower.assign(p->lower, p->lower + d);
   h->upper.assign(p->upper, p->upper + d);

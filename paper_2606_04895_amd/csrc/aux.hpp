@@ -59,8 +59,10 @@ hipError_t launch_ess_param_stats(const double* mean, const double* ssq, int64_t
 hipError_t launch_ess_autocov(const float* rec, const double* mean, int64_t T, int d, int64_t N,
                               int64_t lag0, int n_win, int n_seg, double* part, double* out,
                               hipStream_t s);
+// the rows that plain_bin reads: cos, sin of (2 pi k_m) x_j and (data, weight) of every bin
+hipError_t launch_plain_table(const Target& tg, f64x2* table, hipStream_t s);
 // log pi of a.st.N points a.ex_x into a.ex_lp, plain model alone (plain_mode 2)
-hipError_t launch_plain_eval(const KArgs& a, hipStream_t s);
+hipError_t launch_plain_eval(const KArgs& a, int n_cu, hipStream_t s);
 hipError_t launch_transpose(const double* src, int64_t rows, int64_t cols, double* dst,
                             hipStream_t s);
 struct InputScaling {  // kernel argument: per-component centre and inverse scale

@@ -21,10 +21,9 @@ struct Target {
   const double *train_lo, *train_hi;
   int n_bins, n_terms;
   const double *xgrid, *data, *w2, *pa, *pg, *pp, *pk, *pg0, *pc, *pis;
-  int pl_even;            // the grid is finite and evenly spaced: the recurrence of plain_wave applies
-  double pl_step;         // 64 grid spacings
-  const double* pl_rot;   // [n_terms][2] cos, sin of 2 pi k over pl_step
-  const f64x2* pl_trig;   // [segments][kMaxTerms][64] cos, sin of 2 pi k x at a segment's first bins
+  int pl_even;          // the grid is finite and evenly spaced: the recurrence of plain_wave applies
+  double pl_step;       // 64 grid spacings
+  const f64x2* pl_tab;  // [ceil(n_bins / 64)][n_terms + 1][64]: cos, sin of (2 pi k) x; data, weight
   int box_penalty;  // 1: smooth penalty outside the prior box instead of -inf
   double pen_w;     // its width w (in box widths)
 };
@@ -336,107 +335,193 @@ __device__ __forceinline__ double lane_value(double v, int m) {
   return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
-// Plain spectrum log-likelihood of one chain by one wave, without the gradient (training data,
-// importance weights, MH and the ensemble moves); lane l takes bins l, l + 64, ...  Term m's
-// amplitude times its damped oscillation, as a complex number
-//   w_m(j) = a_m exp(-gamma_m x_j) exp(i (2 pi k_m x_j + phi_m)),
-// advances over an evenly spaced grid by one complex factor z_m per 64 bins, so a bin costs
-// four FP64 multiply-adds per term instead of an exponential and a sine and cosine.  Each lane
-// starts from its first bin (exp(-gamma x), and the chain-independent cos / sin(2 pi k x) from a
-// table) and restarts from the bin itself every kPlainSeg steps.  Bound by the FP64 rate: 20000
-// points, 2500 bins x 8 terms 318 us in the tile kernels (plain_eval_kernel: 121 us), against 3550 us
-// with exp and sincos per bin and a workgroup per chain.
+// Plain spectrum log-likelihood by one wave per NP chains, without the gradient (training data,
+// importance weights, MH and the ensemble moves); lane l takes bins l, l + 64, ...  Term m at bin j is
+//   a_m exp(-gamma_m x_j) cos(2 pi k_m x_j + phi_m) = u_m(j) cos(2 pi k_m x_j) - v_m(j) sin(2 pi k_m x_j),
+//   (u_m, v_m)(j) = a_m exp(-gamma_m x_j) (cos phi_m, sin phi_m).
+// The cosines and sines do not depend on the chain and come from a table (16 bytes per bin and term,
+// each rounded once); u and v advance over an evenly spaced grid by one real factor per 64 bins, so a
+// bin costs four FP64 multiply-adds per term instead of an exponential, a sine and a cosine.  A
+// chain's value does not depend on NP.
 //
-// The recurrence holds where no factor of a term leaves the range of FP64 anywhere on the grid: a
-// seed that underflows would leave a term that grows along the grid (a descending grid, a negative
-// damping) at zero, one that overflows would turn a decaying term into NaN.  -gamma x is largest and
-// smallest at the ends of the grid, so |ln a| and |gamma x| there at most kPlainExp bound every
-// product by exp(+-2 kPlainExp).  A chain with a term outside (NaN included), and every chain on a
-// grid that is not evenly spaced or not finite, is evaluated bin by bin with the expressions of
+// Rounding.  The factor is applied as u + u expm1(-gamma h): its own rounding, the same at every
+// step, enters as a share |gamma h| of an ulp, and what is left are the independent roundings of the
+// results.  Every kPlainSeg steps u and v start again from exp(-gamma x) itself; for a term that grows
+// along the grid, whose early roundings would count most at its largest values, before it has grown by
+// a factor exp(kPlainStep), and at every step once a single one decays by more than that.  2500 bins x 8
+// terms, x = 0 .. 1, k up to 24, rms relative error of log pi: 6.3e-16 here, 7.1e-16 with an
+// exponential and a cosine per bin, 4.8e-15 when the whole complex oscillation was advanced by one
+// rounded complex factor.
+//
+// Range.  The recurrence holds where no factor of a term leaves the range of FP64 anywhere on the
+// grid: a start that underflows would leave a term that grows along the grid (a descending grid, a
+// negative damping) at zero, one that overflows would turn a decaying term into NaN.  -gamma x is
+// largest and smallest at the ends of the grid, so |ln a| and |gamma x| there at most kPlainExp bound
+// every product by exp(+-2 kPlainExp).  A chain with a term outside (NaN included), and every chain on
+// a grid that is not evenly spaced or not finite, is evaluated bin by bin with the expressions of
 // plain_chain.
 constexpr int kPlainSeg = 64;
-constexpr double kPlainExp = 300.0;
-__device__ __forceinline__ void plain_wave(const Target& tg, const TView& X, int c, double* outv) {
-  constexpr double kPi = 3.141592653589793;
+constexpr double kPlainExp = 300.0, kPlainStep = 0.5;
+constexpr int64_t kPlainTable = (int64_t)1 << 20;  // bins up to which the table is built
+
+template <int NP>
+struct PlainChains {
+  double A[NP], gm[NP], th[NP], P[NP], Q[NP];  // lane m: term m
+  double f[NP][kMaxTerms], u[NP][kMaxTerms], v[NP][kMaxTerms], ll[NP];
+  int mask[NP];  // u and v start again where (q & mask) == 0
+  bool ok[NP];   // in range for the recurrence
+};
+
+template <int NP>
+__device__ __forceinline__ void plain_begin(const Target& tg, const TView& X, const int (&c)[NP],
+                                            PlainChains<NP>& s) {
   const int lane = local_tid() & 63, d = tg.d, nt = tg.n_terms, nb = tg.n_bins;
   const int li = lane < d ? lane : d - 1, lm = lane < nt ? lane : nt - 1;
-  // lane i: the scaled component i; lane m: term m
-  const double tl = (X(li, c) - tg.pc[li]) * tg.pis[li];
-  double sa = 0, sg = 0, sp = 0;
-  for (int i = 0; i < d; ++i) {
-    const double ti = lane_value(tl, i);
-    sa += tg.pa[lm * d + i] * ti;
-    sg += tg.pg[lm * d + i] * ti;
-    sp += tg.pp[lm * d + i] * ti;
-  }
   const bool own = lane < nt;
-  const double th = tanh(sp), A = own ? exp(sa) : 0.0, gm = own ? tg.pg0[lm] * exp(sg) : 0.0;
-  const bool in = fabs(sa) <= kPlainExp && fabs(gm * tg.xgrid[0]) <= kPlainExp &&
-                  fabs(gm * tg.xgrid[nb - 1]) <= kPlainExp;
-  double ll = 0;
-  if (tg.pl_even && __ballot(own && !in) == 0) {
-    double sph, cph;
-    sincos(kPi * th, &sph, &cph);
-    const double ez = own ? exp(-gm * tg.pl_step) : 0.0;
-    const double Pl = A * cph, Ql = A * sph, zrl = ez * tg.pl_rot[2 * lm], zil = ez * tg.pl_rot[2 * lm + 1];
-    double P[kMaxTerms], Q[kMaxTerms], ga[kMaxTerms], zr[kMaxTerms], zi[kMaxTerms];
 #pragma unroll
-    for (int m = 0; m < kMaxTerms; ++m) {
-      P[m] = lane_value(Pl, m);
-      Q[m] = lane_value(Ql, m);
-      ga[m] = lane_value(gm, m);
-      zr[m] = lane_value(zrl, m);
-      zi[m] = lane_value(zil, m);
+  for (int p = 0; p < NP; ++p) {
+    const double tl = (X(li, c[p]) - tg.pc[li]) * tg.pis[li];  // lane i: the scaled component i
+    double sa = 0, sg = 0, sp = 0;
+    for (int i = 0; i < d; ++i) {
+      const double ti = lane_value(tl, i);
+      sa += tg.pa[lm * d + i] * ti;
+      sg += tg.pg[lm * d + i] * ti;
+      sp += tg.pp[lm * d + i] * ti;
     }
-    double re[kMaxTerms], im[kMaxTerms];
-    for (int j0 = 0; j0 < nb; j0 += 64 * kPlainSeg) {
-      const int js = j0 + lane < nb ? j0 + lane : nb - 1;
-      const double x = tg.xgrid[js];
-      // terms past n_terms have P = Q = z = 0 and stay zero
+    s.A[p] = exp(sa);
+    s.gm[p] = tg.pg0[lm] * exp(sg);
+    s.th[p] = tanh(sp);
+    const bool in = fabs(sa) <= kPlainExp && fabs(s.gm[p] * tg.xgrid[0]) <= kPlainExp &&
+                    fabs(s.gm[p] * tg.xgrid[nb - 1]) <= kPlainExp;
+    s.ok[p] = tg.pl_even && __ballot(own && !in) == 0;
+    const double decay = s.gm[p] * tg.pl_step;
+    int seg = kPlainSeg;
+    while (seg > 1 && __ballot(decay > kPlainStep || -decay * seg > kPlainStep)) seg >>= 1;
+    s.mask[p] = seg - 1;
+    double sph, cph;
+    sincos(3.141592653589793 * s.th[p], &sph, &cph);
+    const bool use = own && s.ok[p];
+    s.P[p] = use ? s.A[p] * cph : 0.0;
+    s.Q[p] = use ? s.A[p] * sph : 0.0;
+    const double fl = use ? expm1(-decay) : 0.0;
+#pragma unroll
+    for (int m = 0; m < kMaxTerms; ++m) s.f[p][m] = lane_value(fl, m);
+    s.ll[p] = 0;
+  }
+}
+
+// u and v at the bins of chunk q (64 bins), where they start again (zero past the last term).
+template <int NP>
+__device__ __forceinline__ void plain_start(const Target& tg, int q, PlainChains<NP>& s) {
+  const int j = q * 64 + (local_tid() & 63);
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    if ((q & s.mask[p]) == 0) {
+      double x = tg.xgrid[j < tg.n_bins ? j : tg.n_bins - 1];
+      asm volatile("" : "+v"(x));  // waited for here, not past the branch behind the table's loads
 #pragma unroll
       for (int m = 0; m < kMaxTerms; ++m) {
-        const f64x2 t = tg.pl_trig[((int64_t)(js / (64 * kPlainSeg)) * kMaxTerms + m) * 64 + (js & 63)];
-        const double e = exp(-ga[m] * x);
-        re[m] = e * (t[0] * P[m] - t[1] * Q[m]);
-        im[m] = e * (t[1] * P[m] + t[0] * Q[m]);
-      }
-      const int j1 = j0 + 64 * kPlainSeg < nb ? j0 + 64 * kPlainSeg : nb;
-      double dat = tg.data[js], w2 = tg.w2[js];
-      for (int jb = j0; jb < j1; jb += 64) {
-        const int j = jb + lane, jn = j + 64 < nb ? j + 64 : nb - 1;
-        const double dn = tg.data[jn], wn = tg.w2[jn];
-        double spec = 0;
-#pragma unroll
-        for (int m = 0; m < kMaxTerms; ++m) spec += re[m];
-        const double dr = j < nb ? spec - dat : 0.0;
-        ll += dr * (dr * w2);
-        dat = dn;
-        w2 = wn;
-#pragma unroll
-        for (int m = 0; m < kMaxTerms; ++m) {
-          const double t = re[m] * zr[m] - im[m] * zi[m];
-          im[m] = im[m] * zr[m] + re[m] * zi[m];
-          re[m] = t;
+        s.u[p][m] = s.v[p][m] = 0.0;
+        if (m < tg.n_terms && s.ok[p]) {
+          const double e = exp(-lane_value(s.gm[p], m) * x);
+          s.u[p][m] = e * lane_value(s.P[p], m);
+          s.v[p][m] = e * lane_value(s.Q[p], m);
         }
       }
     }
-  } else {
-    for (int jb = 0; jb < nb; jb += 64) {
-      const int j = jb + lane, jj = j < nb ? j : nb - 1;
-      const double x = tg.xgrid[jj];
-      double spec = 0;
-      for (int m = 0; m < nt; ++m) {
-        const double e = exp(-lane_value(gm, m) * x);
-        double sn, cs;
-        sincos(2.0 * kPi * tg.pk[m] * x + kPi * lane_value(th, m), &sn, &cs);
-        spec += lane_value(A, m) * (e * cs);
+  }
+}
+
+// One bin per lane: t the cosines and sines of the terms, dw the data and its weight.  Each is replaced
+// by the row of the next chunk once it is used (terms past n_terms: the last one's, times u = v = 0).
+template <int NP>
+__device__ __forceinline__ void plain_bin(const Target& tg, f64x2 (&t)[kMaxTerms], f64x2& dw,
+                                          const f64x2* next, PlainChains<NP>& s) {
+  double spec[NP][2] = {};
+#pragma unroll
+  for (int m = 0; m < kMaxTerms; ++m) {
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      spec[p][m & 1] = fma(t[m][0], s.u[p][m], fma(-t[m][1], s.v[p][m], spec[p][m & 1]));
+      s.u[p][m] = fma(s.u[p][m], s.f[p][m], s.u[p][m]);
+      s.v[p][m] = fma(s.v[p][m], s.f[p][m], s.v[p][m]);
+    }
+    t[m] = next[(m < tg.n_terms ? m : tg.n_terms - 1) * 64];
+  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const double dr = (spec[p][0] + spec[p][1]) - dw[0];
+    s.ll[p] += dr * (dr * dw[1]);
+  }
+  dw = next[tg.n_terms * 64];
+}
+// The chains' log-likelihoods, in every lane; those out of the recurrence's range are evaluated here.
+template <int NP>
+__device__ __forceinline__ void plain_end(const Target& tg, PlainChains<NP>& s, double (&out)[NP]) {
+  constexpr double kPi = 3.141592653589793;
+  const int lane = local_tid() & 63, nb = tg.n_bins;
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    if (!s.ok[p]) {
+      double ll = 0;
+      for (int jb = 0; jb < nb; jb += 64) {
+        const int j = jb + lane, jj = j < nb ? j : nb - 1;
+        const double x = tg.xgrid[jj];
+        double spec = 0;
+#pragma unroll
+        for (int m = 0; m < kMaxTerms; ++m) {
+          if (m < tg.n_terms) {
+            const double e = exp(-lane_value(s.gm[p], m) * x);
+            double sn, cs;
+            sincos(2.0 * kPi * tg.pk[m] * x + kPi * lane_value(s.th[p], m), &sn, &cs);
+            spec += lane_value(s.A[p], m) * (e * cs);
+          }
+        }
+        const double dr = j < nb ? spec - tg.data[jj] : 0.0;
+        ll += dr * (dr * tg.w2[jj]);
       }
-      const double dr = j < nb ? spec - tg.data[jj] : 0.0;
-      ll += dr * (dr * tg.w2[jj]);
+      s.ll[p] = ll;
+    }
+    out[p] = -0.5 * wave_sum(s.ll[p]);
+  }
+}
+
+template <int NP>
+__device__ __forceinline__ void plain_wave(const Target& tg, const TView& X, const int (&c)[NP],
+                                           double (&out)[NP]) {
+  PlainChains<NP> s;
+  plain_begin<NP>(tg, X, c, s);
+  bool any = false, long_seg = true;
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    any = any || s.ok[p];
+    long_seg = long_seg && s.mask[p] == kPlainSeg - 1;
+  }
+  if (any) {
+    const int nt = tg.n_terms, nq = (tg.n_bins + 63) / 64;
+    const f64x2* row = tg.pl_tab + (local_tid() & 63);
+    f64x2 t[kMaxTerms], dw;
+#pragma unroll
+    for (int m = 0; m < kMaxTerms; ++m) t[m] = row[(m < nt ? m : nt - 1) * 64];
+    dw = row[nt * 64];
+    auto bin = [&](int q) {
+      if (q + 1 < nq) row += (nt + 1) * 64;
+      plain_bin(tg, t, dw, row, s);
+    };
+    if (long_seg) {  // the exponentials (and their constants) stay out of the loop
+      for (int q0 = 0; q0 < nq; q0 += kPlainSeg) {
+        plain_start(tg, q0, s);
+        const int q1 = q0 + kPlainSeg < nq ? q0 + kPlainSeg : nq;
+        for (int q = q0; q < q1; ++q) bin(q);
+      }
+    } else {
+      for (int q = 0; q < nq; ++q) {
+        plain_start(tg, q, s);
+        bin(q);
+      }
     }
   }
-  ll = wave_sum(ll);
-  if (lane == 0) *outv = -0.5 * ll;
+  plain_end(tg, s, out);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1193,8 +1278,22 @@ __device__ __forceinline__ void eval_tile(const KArgs& a, char* smem, typename P
         if (!intrain[c]) plain_chain(tg, X, c, true, psc, pv + c, pgr + c * d);
     } else {
       const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-      for (int c = wv; c < mv; c += kWaves)
-        if (!__builtin_amdgcn_readfirstlane(intrain[c])) plain_wave(tg, X, c, pv + c);
+      // this wave's chains that take the plain model, two at a time (they share the table's rows: stretch
+      // moves of 4096 chains in BF16: 168 us a step one by one, 139 in pairs)
+      auto next = [&](int c) {
+        while (c < mv && __builtin_amdgcn_readfirstlane(intrain[c])) c += kWaves;
+        return c;
+      };
+      for (int c = next(wv); c < mv;) {
+        const int c2 = next(c + kWaves);
+        double v[2];
+        plain_wave<2>(tg, X, {c, c2 < mv ? c2 : c}, v);
+        if ((tid & 63) == 0) {
+          pv[c] = v[0];
+          if (c2 < mv) pv[c2] = v[1];
+        }
+        c = next(c2 + kWaves);
+      }
       __syncthreads();
     }
   }

@@ -583,46 +583,80 @@ hipError_t noalloc_scratch_address(int dev, double** p) {
   return hipSuccess;
 }
 
-// ---- batch log pi of the plain model (no gradient): one wave per point -----------------------
+// ---- table of the plain model's oscillations and data -----------------------------------------
+// The argument (2 pi k) x as a sum of two doubles, so that cosine and sine are rounded once; zero
+// rows (weight 0) past the last bin.
+__global__ void plain_table_kernel(Target tg, f64x2* table) {
+  const int rows = tg.n_terms + 1;
+  const int64_t n = (int64_t)(tg.n_bins + 63) / 64 * 64 * rows;
+  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n;
+       e += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t j = e / (64 * rows) * 64 + (e & 63);
+    const int m = (int)(e / 64 % rows);
+    f64x2 v = {0.0, 0.0};
+    if (j < tg.n_bins && m < tg.n_terms) {
+      const double w = 2.0 * 3.141592653589793 * tg.pk[m], x = tg.xgrid[j];
+      const double hi = w * x, lo = fma(w, x, -hi);
+      double sh, ch, sl, cl;
+      sincos(hi, &sh, &ch);
+      sincos(lo, &sl, &cl);
+      v = f64x2{ch * cl - sh * sl, sh * cl + ch * sl};
+    } else if (j < tg.n_bins) {
+      v = f64x2{tg.data[j], tg.w2[j]};
+    }
+    table[e] = v;
+  }
+}
+
+// ---- batch log pi of the plain model (no gradient): NP points per wave ------------------------
 // The tile kernels hold a workgroup per CU with the registers of the emulator passes, one wave per
-// SIMD; here several waves share one, which hides the latency of plain_wave's dependent FP64
-// chains: 20000 points of the 2500-bin model 121 us, against 318 us in 64-point tiles.  The sums of
-// the Gaussian part and of the penalty keep the tile kernels' component order.
-__global__ __launch_bounds__(kAuxThreads) void plain_eval_kernel(KArgs a) {
+// SIMD; here two or three share one.  Bound by the rows of plain_wave's table, 320 KB per wave for 2500
+// bins x 8 terms from L2 (50 B per clock and CU), hence several points per wave, and with few points by
+// the latency of its 40 dependent chunks.  The sums of the Gaussian part and of the penalty keep the
+// tile kernels' component order.
+template <int NP>
+__global__ __launch_bounds__(64) void plain_eval_kernel(KArgs a) {
   const Target& tg = a.tg;
-  const int64_t c = (int64_t)blockIdx.x * (kAuxThreads / 64) + (threadIdx.x >> 6);
-  if (c >= a.st.N) return;
-  const int lane = threadIdx.x & 63, d = tg.d, i = lane < d ? lane : d - 1;
-  __shared__ double out[kAuxThreads / 64];
-  double* pl = out + (threadIdx.x >> 6);
-  const TView X{const_cast<double*>(a.ex_x) + c, a.ex_pitch};
-  plain_wave(tg, X, 0, pl);
-  const double x = X(i, 0);
-  const bool in = __ballot(lane < d && !(x >= tg.lower[i] && x <= tg.upper[i])) == 0;
-  double lp = tg.offset;
-  if (tg.gauss_coef != 0.0) {
-    double y = x;
-    if (tg.tw_v >= 0) {
-      const double du = lane_value(x, tg.tw_u) - tg.tw_center;
-      if (i == tg.tw_v) y = y + tg.tw_beta * (du * du - tg.tw_kappa);
+  const int lane = threadIdx.x, d = tg.d;
+  const int64_t c0 = (int64_t)blockIdx.x * NP;
+  const int mv = a.st.N - c0 < NP ? (int)(a.st.N - c0) : NP;
+  const TView X{const_cast<double*>(a.ex_x) + c0, a.ex_pitch};
+  int c[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) c[p] = p < mv ? p : mv - 1;
+  double pl[NP];
+  plain_wave<NP>(tg, X, c, pl);
+  const int i = lane < d ? lane : d - 1;
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    if (p >= mv) break;
+    const double x = X(i, p);
+    const bool in = __ballot(lane < d && !(x >= tg.lower[i] && x <= tg.upper[i])) == 0;
+    double lp = tg.offset;
+    if (tg.gauss_coef != 0.0) {
+      double y = x;
+      if (tg.tw_v >= 0) {
+        const double du = lane_value(x, tg.tw_u) - tg.tw_center;
+        if (i == tg.tw_v) y = y + tg.tw_beta * (du * du - tg.tw_kappa);
+      }
+      const double R = y - tg.gmean[i];
+      double PR = 0, q = 0;
+      for (int j = 0; j < d; ++j) PR += tg.gprec[i * d + j] * lane_value(R, j);
+      for (int j = 0; j < d; ++j) q += lane_value(R, j) * lane_value(PR, j);
+      lp += tg.gauss_coef * (-0.5 * q);
     }
-    const double R = y - tg.gmean[i];
-    double PR = 0, q = 0;
-    for (int j = 0; j < d; ++j) PR += tg.gprec[i * d + j] * lane_value(R, j);
-    for (int j = 0; j < d; ++j) q += lane_value(R, j) * lane_value(PR, j);
-    lp += tg.gauss_coef * (-0.5 * q);
-  }
-  lp += lane_value(lane == 0 ? *pl : 0.0, 0);
-  if (tg.box_penalty) {
-    if (!in) {
-      double dp;
-      const double pen = box_pen(tg, i, x, &dp);
-      for (int j = 0; j < d; ++j) lp -= lane_value(pen, j);
+    lp += pl[p];
+    if (tg.box_penalty) {
+      if (!in) {
+        double dp;
+        const double pen = box_pen(tg, i, x, &dp);
+        for (int j = 0; j < d; ++j) lp -= lane_value(pen, j);
+      }
+    } else if (!in) {
+      lp = -INFINITY;
     }
-  } else if (!in) {
-    lp = -INFINITY;
+    if (lane == 0) a.ex_lp[c0 + p] = lp;
   }
-  if (lane == 0) a.ex_lp[c] = lp;
 }
 
 // ---- layout conversion: dst[j][i] = src[i][j] for a rows x cols row-major source ----------
@@ -977,10 +1011,23 @@ hipError_t launch_ess_autocov(const float* rec, const double* mean, int64_t T, i
   return hipGetLastError();
 }
 
-hipError_t launch_plain_eval(const KArgs& a, hipStream_t s) {
-  constexpr int64_t w = kAuxThreads / 64;
-  hipLaunchKernelGGL(plain_eval_kernel, dim3((unsigned)((a.st.N + w - 1) / w)), dim3(kAuxThreads), 0, s,
-                     a);
+hipError_t launch_plain_table(const Target& tg, f64x2* table, hipStream_t s) {
+  hipLaunchKernelGGL(plain_table_kernel, dim3(grid_for((int64_t)(tg.n_bins + 63) / 64 * 64 * (tg.n_terms + 1))),
+                     dim3(kAuxThreads), 0, s, tg, table);
+  return hipGetLastError();
+}
+
+// Points per wave: one while the chip's SIMDs (n_cu x 4) get no more than a wave each, then as many as
+// two waves per SIMD hold at once, at most three (us for 1000 / 2048 / 4096 / 6000 / 20000 points: one
+// per wave 17.2 / 28.1 / 49.3 / 69.8 / 224, two 20.5 / 21.3 / 32.9 / 46.4 / 134, three 25.9 / 26.0 / 37.2 /
+// 38.7 / 120; four need more registers than two waves have).
+hipError_t launch_plain_eval(const KArgs& a, int n_cu, hipStream_t s) {
+  const int64_t n = a.st.N;
+  const int np = n <= 4 * n_cu ? 1 : n <= 16 * n_cu ? 2 : 3;
+  const dim3 g((unsigned)((n + np - 1) / np)), b(64);
+  if (np == 1) hipLaunchKernelGGL((plain_eval_kernel<1>), g, b, 0, s, a);
+  else if (np == 2) hipLaunchKernelGGL((plain_eval_kernel<2>), g, b, 0, s, a);
+  else hipLaunchKernelGGL((plain_eval_kernel<3>), g, b, 0, s, a);
   return hipGetLastError();
 }
 
