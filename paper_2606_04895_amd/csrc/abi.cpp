@@ -304,7 +304,7 @@ static int run_eval(best_ctx* h, const double* X, int64_t pitch, int64_t n, doub
   a.ex_lp = LP;
   a.ex_g = G;
   a.ex_grad = G != nullptr;
-  if (a.tg.plain_mode == 2 && !G) {
+  if (a.tg.plain_mode == 2 && !G && (a.tg.pl_even || n > 2)) {  // else: see eval_tile
     HIPCHK(h, launch_plain_eval(a, h->n_cu, h->stream));
     return BEST_OK;
   }

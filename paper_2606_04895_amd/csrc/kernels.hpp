@@ -190,8 +190,8 @@ struct KArgs {
 };
 
 // ---------------------------------------------------------------------------------------
-// Plain spectrum log-likelihood of one chain.  With its gradient: computed by the whole
-// workgroup, an exponential, a sine and a cosine per bin and term.
+// Plain spectrum log-likelihood of one chain, with its gradient if asked for, by the whole workgroup: an
+// exponential, a sine and a cosine per bin and term.
 // ---------------------------------------------------------------------------------------
 // Element (i, c) of a tile's [d][M] FP64 array: the global SoA state (p = base + c0,
 // pitch = Np), a caller's array, or the tile's LDS scratch (pitch = M).
@@ -455,35 +455,69 @@ __device__ __forceinline__ void plain_bin(const Target& tg, f64x2 (&t)[kMaxTerms
   }
   dw = next[tg.n_terms * 64];
 }
-// The chains' log-likelihoods, in every lane; those out of the recurrence's range are evaluated here.
-template <int NP>
-__device__ __forceinline__ void plain_end(const Target& tg, PlainChains<NP>& s, double (&out)[NP]) {
+// Log-likelihood of a chain bin by bin (lane m holds term m's a, gamma and phase / pi).  The sines
+// and cosines of a bin are independent chains of instructions: eight terms at once, unguarded, for more than
+// four (2048 points on an uneven grid: 8 terms 150 us, 220 one by one; 2 terms 140 and 63).
+__device__ __forceinline__ double plain_direct(const Target& tg, double A, double gm, double th) {
   constexpr double kPi = 3.141592653589793;
-  const int lane = local_tid() & 63, nb = tg.n_bins;
-#pragma unroll
-  for (int p = 0; p < NP; ++p) {
-    if (!s.ok[p]) {
-      double ll = 0;
-      for (int jb = 0; jb < nb; jb += 64) {
-        const int j = jb + lane, jj = j < nb ? j : nb - 1;
-        const double x = tg.xgrid[jj];
-        double spec = 0;
-#pragma unroll
-        for (int m = 0; m < kMaxTerms; ++m) {
-          if (m < tg.n_terms) {
-            const double e = exp(-lane_value(s.gm[p], m) * x);
-            double sn, cs;
-            sincos(2.0 * kPi * tg.pk[m] * x + kPi * lane_value(s.th[p], m), &sn, &cs);
-            spec += lane_value(s.A[p], m) * (e * cs);
-          }
-        }
-        const double dr = j < nb ? spec - tg.data[jj] : 0.0;
-        ll += dr * (dr * tg.w2[jj]);
-      }
-      s.ll[p] = ll;
+  const int lane = local_tid() & 63, nb = tg.n_bins, nt = tg.n_terms;
+  double ll = 0;
+  auto sum = [&](auto term) {
+    for (int jb = 0; jb < nb; jb += 64) {
+      const int j = jb + lane, jj = j < nb ? j : nb - 1;
+      const double x = tg.xgrid[jj];
+      double spec = 0;
+      term(x, spec);
+      const double dr = j < nb ? spec - tg.data[jj] : 0.0;
+      ll += dr * (dr * tg.w2[jj]);
     }
-    out[p] = -0.5 * wave_sum(s.ll[p]);
+  };
+  auto value = [&](int m, int mm, double x) {
+    const double e = exp(-lane_value(gm, mm) * x);
+    double sn, cs;
+    sincos(2.0 * kPi * tg.pk[mm] * x + kPi * lane_value(th, mm), &sn, &cs);
+    const double v = lane_value(A, mm) * (e * cs);
+    return m == mm ? v : 0.0;
+  };
+  if (nt > 4) {
+    sum([&](double x, double& spec) {
+#pragma unroll
+      for (int m = 0; m < kMaxTerms; ++m) spec += value(m, m < nt ? m : nt - 1, x);
+    });
+  } else {
+    sum([&](double x, double& spec) {
+      for (int m = 0; m < nt; ++m) spec += value(m, m, x);
+    });
   }
+  return ll;
+}
+
+// The chains' log-likelihoods, in every lane; those out of the recurrence's range are evaluated here
+// (a chain that appears twice, once).
+template <int NP>
+__device__ __forceinline__ void plain_end(const Target& tg, const int (&c)[NP], PlainChains<NP>& s,
+                                          double (&out)[NP]) {
+#pragma unroll 1
+  for (int p = 0; p < NP; ++p) {
+    double A = s.A[0], gm = s.gm[0], th = s.th[0];
+    bool todo = !s.ok[0];
+#pragma unroll
+    for (int r = 1; r < NP; ++r)
+      if (p == r) {
+        A = s.A[r];
+        gm = s.gm[r];
+        th = s.th[r];
+        todo = !s.ok[r] && c[r] != c[0];
+      }
+    if (todo) {
+      const double ll = plain_direct(tg, A, gm, th);
+#pragma unroll
+      for (int r = 0; r < NP; ++r)
+        if (p == r) s.ll[r] = ll;
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p) out[p] = -0.5 * wave_sum(s.ll[p]);
 }
 
 template <int NP>
@@ -521,7 +555,7 @@ __device__ __forceinline__ void plain_wave(const Target& tg, const TView& X, con
       }
     }
   }
-  plain_end(tg, s, out);
+  plain_end(tg, c, s, out);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1273,9 +1307,11 @@ __device__ __forceinline__ void eval_tile(const KArgs& a, char* smem, typename P
   double* pgr = pv + M;        // [M][d]
   double* psc = pgr + M * d;   // plain scratch
   if (tg.plain_mode != 0) {
-    if (grad) {
+    // one or two chains on an uneven grid, bin by bin, are quicker by the whole workgroup (8 terms, one
+    // point 40 us against 74 by a wave, four 156 against 86)
+    if (grad || (!tg.pl_even && mv < 3)) {
       for (int c = 0; c < mv; ++c)
-        if (!intrain[c]) plain_chain(tg, X, c, true, psc, pv + c, pgr + c * d);
+        if (!intrain[c]) plain_chain(tg, X, c, grad, psc, pv + c, pgr + c * d);
     } else {
       const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
       // this wave's chains that take the plain model, two at a time (they share the table's rows: stretch

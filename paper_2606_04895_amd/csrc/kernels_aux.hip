@@ -1020,10 +1020,10 @@ hipError_t launch_plain_table(const Target& tg, f64x2* table, hipStream_t s) {
 // Points per wave: one while the chip's SIMDs (n_cu x 4) get no more than a wave each, then as many as
 // two waves per SIMD hold at once, at most three (us for 1000 / 2048 / 4096 / 6000 / 20000 points: one
 // per wave 17.2 / 28.1 / 49.3 / 69.8 / 224, two 20.5 / 21.3 / 32.9 / 46.4 / 134, three 25.9 / 26.0 / 37.2 /
-// 38.7 / 120; four need more registers than two waves have).
+// 38.7 / 120; four need more registers than two waves have).  Without the table there is nothing to share.
 hipError_t launch_plain_eval(const KArgs& a, int n_cu, hipStream_t s) {
   const int64_t n = a.st.N;
-  const int np = n <= 4 * n_cu ? 1 : n <= 16 * n_cu ? 2 : 3;
+  const int np = n <= 4 * n_cu || !a.tg.pl_even ? 1 : n <= 16 * n_cu ? 2 : 3;
   const dim3 g((unsigned)((n + np - 1) / np)), b(64);
   if (np == 1) hipLaunchKernelGGL((plain_eval_kernel<1>), g, b, 0, s, a);
   else if (np == 2) hipLaunchKernelGGL((plain_eval_kernel<2>), g, b, 0, s, a);

@@ -94,3 +94,17 @@ def test_a_nan_in_the_grid_gives_nan(mode, prec):
     x = np.repeat(0.5 * (p["lower"] + p["upper"])[:, None], 5, axis=1)
     got = B.best_logL_grad(ctx, torch.tensor(x, device="cuda"), want_grad=False)[0]
     assert torch.isnan(got).all()
+
+
+@pytest.mark.parametrize("nt", [1, 4, 5, 8])
+@pytest.mark.parametrize("n", [1, 2, 3, 40])
+@pytest.mark.parametrize("mode,prec", ROUTES)
+def test_uneven_grids(mode, prec, n, nt):
+    """One and two points go to a workgroup each, more to a wave each; up to four terms one by one,
+    more together."""
+    p = _problem(np.linspace(0.0, 1.0, 300) ** 1.3, 0.5 * np.arange(1, nt + 1), mode, 1.0)
+    rng = np.random.default_rng(n)
+    x = p["lower"] + rng.random((n, p["d"])) * 0.99 * (p["upper"] - p["lower"])
+    ctx = B.best_init(p, n_chains=16, precision=prec, seed=1)
+    got = B.best_logL_grad(ctx, torch.tensor(x.T.copy(), device="cuda"), want_grad=False)[0]
+    np.testing.assert_allclose(got.cpu().numpy(), _reference(p, x), rtol=1e-11)
