@@ -1530,9 +1530,7 @@ int best_sliced_wasserstein(best_ctx* h, const float* a, int64_t Ta, int64_t cha
   const int d = h->d;
   const int64_t na = Ta * chains_a, nb = Tb * chains_b, n = na + nb;
   if (n >= ((int64_t)1 << 31)) return fail(h, BEST_EINVAL, "more than 2^31 - 1 draws");
-  // projections per batch: two key buffers of up to 2^23 keys, which the last-level cache holds
-  // between the passes of a batch
-  const int P = (int)std::max<int64_t>(1, std::min<int64_t>(n_proj, ((int64_t)1 << 23) / n));
+  const int P = (int)sliced_batch(n, n_proj);
   int rc;
   if ((rc = check_whitening(h, mu, L))) return rc;
   const size_t bw = (size_t)d * (d + 1) * 8, ba = (size_t)d * na * 8, bb = (size_t)d * nb * 8,

@@ -2,6 +2,7 @@
 // unit that defines the kernel it launches.
 #pragma once
 #include "train.hpp"
+#include "launch.hpp"
 
 namespace best {
 

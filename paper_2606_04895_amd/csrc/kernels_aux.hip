@@ -388,29 +388,32 @@ __global__ __launch_bounds__(64 * kStatWaves) void ess_chain_stats_kernel(const 
                                                                           double* ssq) {
   __shared__ double sh[2][kStatWaves][64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, i = blockIdx.y;
-  const int64_t c = (int64_t)blockIdx.x * 64 + lane;
-  const float* __restrict__ x = rec + (int64_t)i * N + (c < N ? c : N - 1);
   const int64_t st = (int64_t)d * N;
-  const double x0 = x[0];
-  double s1 = 0, s2 = 0;
+  for (int64_t cb = blockIdx.x; cb * 64 < N; cb += gridDim.x) {
+    const int64_t c = cb * 64 + lane;
+    const float* __restrict__ x = rec + (int64_t)i * N + (c < N ? c : N - 1);
+    const double x0 = x[0];
+    double s1 = 0, s2 = 0;
 #pragma unroll 8
-  for (int64_t t = wv; t < T; t += kStatWaves) {
-    const double u = (double)x[t * st] - x0;
-    s1 += u;
-    s2 += u * u;
-  }
-  sh[0][wv][lane] = s1;
-  sh[1][wv][lane] = s2;
-  __syncthreads();
-  if (wv == 0 && c < N) {
-    s1 = s2 = 0;
-    for (int w = 0; w < kStatWaves; ++w) {
-      s1 += sh[0][w][lane];
-      s2 += sh[1][w][lane];
+    for (int64_t t = wv; t < T; t += kStatWaves) {
+      const double u = (double)x[t * st] - x0;
+      s1 += u;
+      s2 += u * u;
     }
-    mean[i * N + c] = x0 + s1 / (double)T;
-    const double q = s2 - s1 * s1 / (double)T;
-    ssq[i * N + c] = q < 0.0 ? 0.0 : q;  // NaN passes
+    sh[0][wv][lane] = s1;
+    sh[1][wv][lane] = s2;
+    __syncthreads();
+    if (wv == 0 && c < N) {
+      s1 = s2 = 0;
+      for (int w = 0; w < kStatWaves; ++w) {
+        s1 += sh[0][w][lane];
+        s2 += sh[1][w][lane];
+      }
+      mean[i * N + c] = x0 + s1 / (double)T;
+      const double q = s2 - s1 * s1 / (double)T;
+      ssq[i * N + c] = q < 0.0 ? 0.0 : q;  // NaN passes
+    }
+    __syncthreads();
   }
 }
 
@@ -980,7 +983,7 @@ hipError_t launch_moments(const float* rec, const double* xs, int64_t T, int64_t
 
 hipError_t launch_ess_chain_stats(const float* rec, int64_t T, int d, int64_t N, double* mean,
                                   double* ssq, hipStream_t s) {
-  hipLaunchKernelGGL(ess_chain_stats_kernel, dim3((unsigned)((N + 63) / 64), (unsigned)d),
+  hipLaunchKernelGGL(ess_chain_stats_kernel, dim3((unsigned)capped_blocks((N + 63) / 64, 64 * kStatWaves), (unsigned)d),
                      dim3(64 * kStatWaves), 0, s, rec, T, d, N, mean, ssq);
   return hipGetLastError();
 }
@@ -1021,14 +1024,25 @@ hipError_t launch_plain_table(const Target& tg, f64x2* table, hipStream_t s) {
 // two waves per SIMD hold at once, at most three (us for 1000 / 2048 / 4096 / 6000 / 20000 points: one
 // per wave 17.2 / 28.1 / 49.3 / 69.8 / 224, two 20.5 / 21.3 / 32.9 / 46.4 / 134, three 25.9 / 26.0 / 37.2 /
 // 38.7 / 120; four need more registers than two waves have).  Without the table there is nothing to share.
+// A grid has fewer than 2^32 work items: larger batches are split here (a loop over the points in the
+// kernel keeps 50 registers more alive, one wave per SIMD fewer).
 hipError_t launch_plain_eval(const KArgs& a, int n_cu, hipStream_t s) {
   const int64_t n = a.st.N;
   const int np = n <= 4 * n_cu || !a.tg.pl_even ? 1 : n <= 16 * n_cu ? 2 : 3;
-  const dim3 g((unsigned)((n + np - 1) / np)), b(64);
-  if (np == 1) hipLaunchKernelGGL((plain_eval_kernel<1>), g, b, 0, s, a);
-  else if (np == 2) hipLaunchKernelGGL((plain_eval_kernel<2>), g, b, 0, s, a);
-  else hipLaunchKernelGGL((plain_eval_kernel<3>), g, b, 0, s, a);
-  return hipGetLastError();
+  KArgs k = a;
+  for (int64_t c = 0; c < n;) {
+    const int64_t blocks = capped_blocks((n - c + np - 1) / np, 64);
+    k.st.N = n - c < blocks * np ? n - c : blocks * np;
+    k.ex_x = a.ex_x + c;
+    k.ex_lp = a.ex_lp + c;
+    const dim3 g((unsigned)blocks), b(64);
+    if (np == 1) hipLaunchKernelGGL((plain_eval_kernel<1>), g, b, 0, s, k);
+    else if (np == 2) hipLaunchKernelGGL((plain_eval_kernel<2>), g, b, 0, s, k);
+    else hipLaunchKernelGGL((plain_eval_kernel<3>), g, b, 0, s, k);
+    if (hipError_t e = hipGetLastError()) return e;
+    c += k.st.N;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_transpose(const double* src, int64_t rows, int64_t cols, double* dst,
