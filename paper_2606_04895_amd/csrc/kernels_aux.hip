@@ -376,42 +376,83 @@ __global__ __launch_bounds__(kAuxThreads) void moments_final_kernel(
 
 // ---- ESS ----------------------------------------------------------------------------------
 // Per-chain mean and sum of squared deviations: a workgroup holds 64 chains of one parameter, its
-// 16 waves every 16th step each, so a record of few chains still fills the chip.  One pass: the
-// sums are taken about the chain's first value x_0 (ssq = S2 - S1^2 / T; x_0 is one of the T values,
-// so S2 is at most T + 1 times ssq and the subtraction costs no more than T 2^-53).  Bound by the
-// record's bytes.  4000 x 6 x 4096 (393 MB): 97 us; a thread per chain with two passes took
-// 3190 us.
-constexpr int kStatWaves = 16;
+// 16 waves every 16th step each, so a record of few chains still fills the chip.  One pass over the
+// record: a wave sums eight values at a time about the first of them (their squares are at most nine
+// times the block's deviations), the squares of its blocks are combined by the pairwise formula (Chan,
+// Golub & LeVeque 1979),
+//   ssq += ssq_b + (mean_b - mean)^2 n n_b / (n + n_b),
+// and those of the waves by their distances from the common mean, so that the error is that of two
+// passes wherever the chain starts.  (As S2 - S1^2 / T about the chain's first value it grows T times for
+// a chain that starts far from its mean.)  Means are taken relative to that first value, from which
+XX
+// as S2 - S1^2 / T); a thread per chain with two passes took 3190 us.
+constexpr int kStatWaves = 16, kStatBlock = 8;
+struct StatSteps {  // the first waves have n_hi steps each, the others one less; reciprocals (0 of 0)
+  int64_t n_hi;
+  double r_T, r_hi, r_lo, tail_hi, tail_lo;  // tail: of the steps in the last block
+};
 __global__ __launch_bounds__(64 * kStatWaves) void ess_chain_stats_kernel(const float* rec,
                                                                           int64_t T, int d,
-                                                                          int64_t N, double* mean,
+                                                                          int64_t N, StatSteps n,
+                                                                          double* mean,
                                                                           double* ssq) {
   __shared__ double sh[2][kStatWaves][64];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, i = blockIdx.y;
+  const int lane = threadIdx.x & 63, i = blockIdx.y;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t st = (int64_t)d * N;
+  const int64_t n_w = (T - wv + kStatWaves - 1) / kStatWaves;  // steps of this wave, wv, wv + 16, ..
   for (int64_t cb = blockIdx.x; cb * 64 < N; cb += gridDim.x) {
     const int64_t c = cb * 64 + lane;
-    const float* __restrict__ x = rec + (int64_t)i * N + (c < N ? c : N - 1);
-    const double x0 = x[0];
-    double s1 = 0, s2 = 0;
-#pragma unroll 8
-    for (int64_t t = wv; t < T; t += kStatWaves) {
-      const double u = (double)x[t * st] - x0;
-      s1 += u;
-      s2 += u * u;
+    const unsigned cl = (unsigned)(c < N ? lane : N - 1 - cb * 64);
+    const float* __restrict__ x = rec + (int64_t)i * N + cb * 64;  // scalar; lane offset cl
+    const double x0 = x[cl];
+    double s1 = 0, q = 0, rk = 0;  // over the wave's first k values: sum, squares about their mean, 1 / k
+    float next[kStatBlock];
+    auto load = [&](int64_t k) {
+      const float* p = x + (wv + k * kStatWaves) * st;
+#pragma unroll
+      for (int u = 0; u < kStatBlock; ++u) {
+        next[u] = p[cl];
+        if (k + u + 1 < n_w) p += kStatWaves * st;
+      }
+    };
+    if (n_w > 0) load(0);
+    for (int64_t k = 0; k < n_w; k += kStatBlock) {
+      const int nb = n_w - k < kStatBlock ? (int)(n_w - k) : kStatBlock;
+      float v[kStatBlock];
+#pragma unroll
+      for (int u = 0; u < kStatBlock; ++u) v[u] = next[u];
+      if (k + kStatBlock < n_w) load(k + kStatBlock);
+      const double c0 = v[0];
+      double sb = 0, qb = 0;
+#pragma unroll
+      for (int u = 1; u < kStatBlock; ++u) {
+        const double y = u < nb ? (double)v[u] - c0 : 0.0;
+        sb += y;
+        qb += y * y;
+      }
+      const double rb = k + kStatBlock <= n_w ? 1.0 / kStatBlock : n_w == n.n_hi ? n.tail_hi : n.tail_lo;
+      const double off = c0 - x0, dm = k ? (off + sb * rb) - s1 * rk : 0.0;
+      rk = k + nb < n_w ? 1.0 / (double)(k + nb) : n_w == n.n_hi ? n.r_hi : n.r_lo;
+      q += (qb - sb * (sb * rb)) + dm * dm * ((double)k * (double)nb * rk);
+      s1 += off * (double)nb + sb;
     }
     sh[0][wv][lane] = s1;
-    sh[1][wv][lane] = s2;
+    sh[1][wv][lane] = q;
     __syncthreads();
     if (wv == 0 && c < N) {
-      s1 = s2 = 0;
+      s1 = q = 0;
+#pragma unroll 4
+      for (int w = 0; w < kStatWaves; ++w) s1 += sh[0][w][lane];  // zero for a wave without steps
+      const double m = s1 * n.r_T;
+#pragma unroll 4
       for (int w = 0; w < kStatWaves; ++w) {
-        s1 += sh[0][w][lane];
-        s2 += sh[1][w][lane];
+        const int64_t nw = (T - w + kStatWaves - 1) / kStatWaves;
+        const double dm = sh[0][w][lane] * (nw == n.n_hi ? n.r_hi : n.r_lo) - m;
+        q += sh[1][w][lane] + (double)nw * (dm * dm);
       }
-      mean[i * N + c] = x0 + s1 / (double)T;
-      const double q = s2 - s1 * s1 / (double)T;
-      ssq[i * N + c] = q < 0.0 ? 0.0 : q;  // NaN passes
+      mean[i * N + c] = x0 + m;
+      ssq[i * N + c] = q;
     }
     __syncthreads();
   }
@@ -983,8 +1024,12 @@ hipError_t launch_moments(const float* rec, const double* xs, int64_t T, int64_t
 
 hipError_t launch_ess_chain_stats(const float* rec, int64_t T, int d, int64_t N, double* mean,
                                   double* ssq, hipStream_t s) {
-  hipLaunchKernelGGL(ess_chain_stats_kernel, dim3((unsigned)capped_blocks((N + 63) / 64, 64 * kStatWaves), (unsigned)d),
-                     dim3(64 * kStatWaves), 0, s, rec, T, d, N, mean, ssq);
+  const int64_t hi = (T + kStatWaves - 1) / kStatWaves, lo = hi - 1;
+  auto inv = [](int64_t n) { return n ? 1.0 / (double)n : 0.0; };
+  const StatSteps n{hi, 1.0 / (double)T, inv(hi), inv(lo), inv(hi % kStatBlock), inv(lo % kStatBlock)};
+  hipLaunchKernelGGL(ess_chain_stats_kernel,
+                     dim3((unsigned)capped_blocks((N + 63) / 64, 64 * kStatWaves), (unsigned)d),
+                     dim3(64 * kStatWaves), 0, s, rec, T, d, N, n, mean, ssq);
   return hipGetLastError();
 }
 
