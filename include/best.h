@@ -237,8 +237,9 @@ int best_adapt(best_ctx *h, const best_adapt_params *p, best_adapt_info *out);
  * nothing; plain_mode 2 gives zeros.  The prior box is ignored (the gradient of the
  * unbounded expression, as for best_logL_grad).  x: device [d][n]; upstream: device [n]
  * FP64, NULL for all ones; grad_params: device FP64 [best_mlp_nparams].  Asynchronous on
- * the context's stream.  The first call (or a larger n) allocates (2 nh + 2) width + d + 1
- * floats per point, n rounded up to 16 (BEST_ENOMEM).  FP64 contexts: BEST_ESTATE. */
+ * the context's stream.  The first call (or a larger n) allocates 2 nh width + d + 1 floats
+ * per point, n rounded up to 16, and for nh > 1 two panels of width GEMM values per point of at
+ * most 65536 points (BEST_ENOMEM).  FP64 contexts: BEST_ESTATE. */
 int best_logL_param_grad(best_ctx *h, const double *x, int64_t n, const double *upstream,
                          double *grad_params);
 

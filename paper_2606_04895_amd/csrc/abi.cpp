@@ -117,7 +117,8 @@ struct Arena {
 };
 
 // Buffers of a layer-by-layer forward and reverse pass over up to `cap` points (a multiple of
-// 16): (2 nh + 2) H + d + 1 floats per point (the panels 2 H 16-bit values for those types).
+// 16): 2 nh H + d + 1 floats per point, and for more than one hidden layer two panels of H values of the
+// GEMM type per point of at most kFitPanel points.
 struct FitBufs {
   float *act = nullptr, *hx = nullptr, *th = nullptr, *up = nullptr;
   char *pp0 = nullptr, *pp1 = nullptr;
@@ -126,16 +127,17 @@ struct FitBufs {
     if (ldb <= cap) return true;
     for (void* q : {(void*)act, (void*)hx, (void*)th, (void*)up, (void*)pp0, (void*)pp1}) m.release(q);
     *this = FitBufs{};
-    const size_t rows = (size_t)nh * H, panel = (size_t)H * tsize(prec);
+    const size_t rows = (size_t)nh * H;
+    const size_t panel = nh > 1 ? (size_t)std::min(ldb, kFitPanel) * H * tsize(prec) : 1;
     if (m.alloc(&act, rows * ldb) != hipSuccess || m.alloc(&hx, rows * ldb) != hipSuccess ||
         m.alloc(&th, (size_t)d * ldb) != hipSuccess || m.alloc(&up, (size_t)ldb) != hipSuccess ||
-        m.alloc(&pp0, panel * ldb) != hipSuccess || m.alloc(&pp1, panel * ldb) != hipSuccess)
+        m.alloc(&pp0, panel) != hipSuccess || m.alloc(&pp1, panel) != hipSuccess)
       return false;
     cap = ldb;
     return true;
   }
   void fill(FitArgs& a, int64_t n) const {
-    a.n = n;
+    a.n = a.n_batch = n;
     a.ldb = (n + 15) / 16 * 16;
     a.act = act;
     a.hx = hx;

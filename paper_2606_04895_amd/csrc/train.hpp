@@ -204,14 +204,17 @@ __global__ __launch_bounds__(256) void adam_pack_kernel(AdamArgs a, int n_hidden
 //        hx) by the wave that read it last, so the two share the memory.
 //   hx   h_l in the weight-gradient order: lane (q, r) holds points 4q .. 4q + 3 of row r.
 //   pp   two panels [CT][16 H] of the GEMM type in B-fragment order: the 16-bit activations of
-//        the layer just computed in the forward pass, the deltas in the reverse pass.
+//        the layer just computed in the forward pass, the deltas in the reverse pass.  A batch goes
+//        through the layers kFitPanel points at a time (columns are independent), which bounds them.
 // Every output keeps the accumulation order of the tile engine (one accumulator per output,
 // k-steps ascending), and the sums over the output weights its wave order, so the results are
 // those of the tile engine bit for bit.
 // ---------------------------------------------------------------------------------------
+constexpr int64_t kFitPanel = 65536;
 struct FitArgs {
   MlpParams mp;
-  int64_t n, ldb;   // points, and points rounded up to whole column tiles
+  int64_t n, ldb;   // points of this pass; of the batch, rounded up to whole column tiles (strides)
+  int64_t n_batch;  // points of the batch
   int round_h;      // the reverse pass takes h_l rounded to the GEMM type
   // training minibatch: rows perm[batch0 ..] of t_in [.][d] with targets y
   const float *t_in, *y;
@@ -322,7 +325,7 @@ __global__ __launch_bounds__(256) void fit_input_kernel(FitArgs a) {
     ((f32x4*)a.act)[o + lane] = h;
     if constexpr (!EVAL) ((f32x4*)a.hx)[o + dw_slot(lane)] = quad_transpose(h, lane);
     if constexpr (sizeof(typename P::T) == 2)
-      panel_store<P>(a, (typename P::T*)a.pp0, ct, rt, lane, h);
+      if (a.mp.nh > 1) panel_store<P>(a, (typename P::T*)a.pp0, ct, rt, lane, h);
   }
 }
 
@@ -340,7 +343,7 @@ __global__ __launch_bounds__(256) void fit_layer_kernel(FitArgs a, int l) {
   using frag = typename P::frag;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane >> 4;
   const int H = a.mp.H, KS = H / P::KSTEP, RT = H / 16, nrow = RT / (4 * R);
-  const int64_t CT = a.ldb >> 4;
+  const int64_t CT = (a.n + 15) >> 4;
   const int t = xcd_run(blockIdx.x, gridDim.x);
   const int rt0 = ((t % nrow) * 4 + wv) * R;
   const int64_t ct0 = (int64_t)(t / nrow) * C;
@@ -349,7 +352,7 @@ __global__ __launch_bounds__(256) void fit_layer_kernel(FitArgs a, int l) {
   const int par = (a.mp.nh - 1 - l) & 1;  // reverse pass: delta_{nh-1} is in pp0
   const T* Bin;
   if constexpr (BWD) Bin = (const T*)(EVAL && l == a.mp.nh - 1 ? a.pp2 : par ? a.pp1 : a.pp0);
-  else if constexpr (sizeof(T) == 4) Bin = (const T*)a.act + (l - 1) * CT * 16 * H;
+  else if constexpr (sizeof(T) == 4) Bin = (const T*)a.act + (l - 1) * a.ldb * H;
   else Bin = (const T*)((l & 1) ? a.pp0 : a.pp1);
   const frag* __restrict__ B[C];
 #pragma unroll
@@ -497,13 +500,13 @@ __global__ __launch_bounds__(kThreads) void fit_output_kernel(FitArgs a) {
       for (int w = 1; w < kWaves; ++w) o += outp[w][tid];
       o = o + Wo[H];
       if (c < a.n) r = (double)o - (double)a.y[a.perm[a.batch0 + c]];
-      u = (float)(2.0 * r / (double)a.n);
+      u = (float)(2.0 * r / (double)a.n_batch);
     } else if (c < a.n) {
       bool use = a.tg.plain_mode == 0;
       if (a.tg.plain_mode == 1) {
         use = true;
         for (int i = 0; i < a.mp.d; ++i) {
-          const double xv = a.x[i * a.n + c];
+          const double xv = a.x[i * a.x_pitch + c];
           use = use && xv >= a.tg.train_lo[i] && xv <= a.tg.train_hi[i];
         }
       }
