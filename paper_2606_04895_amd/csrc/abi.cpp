@@ -555,7 +555,6 @@ static int upload_problem(best_ctx* h, const best_problem* p) {
       HIPCHK(h, m.alloc((f64x2**)&t.pl_tab, (nb + 63) / 64 * 64 * (nt + 1)));
       HIPCHK(h, launch_plain_table(t, (f64x2*)t.pl_tab, s));
     }
-    HIPCHK(h, m.upload((Target**)&t.dev, &t, 1, s));
   }
   h->lower.assign(p->lower, p->lower + d);
   h->upper.assign(p->upper, p->upper + d);

@@ -24,7 +24,6 @@ struct Target {
   int pl_even;          // the grid is finite and evenly spaced: the recurrence of plain_wave applies
   double pl_step;       // 64 grid spacings
   const f64x2* pl_tab;  // [ceil(n_bins / 64)][n_terms + 1][64]: cos, sin of (2 pi k) x; data, weight
-  const Target* dev;    // a copy in device memory (its plain-model fields)
   int box_penalty;  // 1: smooth penalty outside the prior box instead of -inf
   double pen_w;     // its width w (in box widths)
 };
@@ -559,37 +558,23 @@ __device__ __forceinline__ void plain_wave(const Target& tg, const TView& X, con
   plain_end(tg, c, s, out);
 }
 
-// The plain model's values of a tile's chains c < mv with intrain[c] == 0 into pv[c].  Called, not
-// inlined: inside the tile kernels its registers and code cost the emulator passes that never come here
-// (inlined / called: ten stretch moves on 12 -> 1024 x 4 in FP16 2.02 / 1.92 ms, 296 chains of
-// differential evolution on 6 -> 512 x 4 in BF16 63.8 / 61.9 us a step, one point of 6 -> 128 x 2 17.3 /
-// 15.8 us); the call saves and restores registers (4096 chains on the plain model in BF16: Metropolis-
-// Hastings 66 / 91 us a step, stretch moves 139 / 192, by the workgroup forms 446 and 815).  Each wave takes
-// its chains two at a time, which share the table's rows.
-__device__ __noinline__ void plain_tile(const Target* dev, double* xp, int64_t pitch, int mv,
-                                        const int* intrain, double* pv) {
-  const unsigned long long b = (unsigned long long)dev;
-  const unsigned lo = __builtin_amdgcn_readfirstlane((int)(unsigned)b);
-  const unsigned hi = __builtin_amdgcn_readfirstlane((int)(unsigned)(b >> 32));
-  const Target& tg = *(const Target*)(((unsigned long long)hi << 32) | lo);
-  const int tid = local_tid(), wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  mv = __builtin_amdgcn_readfirstlane(mv);
-  const TView X{xp, pitch};
-  auto next = [&](int c) {
-    while (c < mv && __builtin_amdgcn_readfirstlane(intrain[c])) c += kWaves;
-    return c;
-  };
-  for (int c = next(wv); c < mv;) {
-    const int c2 = next(c + kWaves);
-    double v[2];
-    plain_wave<2>(tg, X, {c, c2 < mv ? c2 : c}, v);
-    if ((tid & 63) == 0) {
-      pv[c] = v[0];
-      if (c2 < mv) pv[c2] = v[1];
-    }
-    c = next(c2 + kWaves);
-  }
-}
+// A precision whose kernels are launched for targets without the plain model (plain_mode 0) alone and
+// leave its code out: in kernels that evaluate values without a gradient, or may, it would cost the
+// emulator passes registers and placement (ten stretch moves on 12 -> 1024 x 4 in FP16 2.02 ms with it,
+// 1.82 without; called instead of inlined, 64-chain tiles in BF16 took 145 us for 16384 points of 6 ->
+// 512 x 4 instead of 89).
+template <class B>
+struct NoPlain : B {};
+template <class B>
+struct InPrec<NoPlain<B>> : InPrec<B> {};
+template <class P>
+struct HasPlain {
+  static constexpr bool value = true;
+};
+template <class B>
+struct HasPlain<NoPlain<B>> {
+  static constexpr bool value = false;
+};
 
 // ---------------------------------------------------------------------------------------
 // Target evaluation for a tile of chains: LPo[c0+c] = log pi(x), GXo = grad_x log pi(x).
@@ -1339,14 +1324,30 @@ __device__ __forceinline__ void eval_tile(const KArgs& a, char* smem, typename P
   double* pv = PR + d * M;     // [M]
   double* pgr = pv + M;        // [M][d]
   double* psc = pgr + M * d;   // plain scratch
-  if (tg.plain_mode != 0) {
+  if constexpr (HasPlain<P>::value) {
     // one or two chains on an uneven grid, bin by bin, are quicker by the whole workgroup (8 terms, one
     // point 40 us against 74 by a wave, four 156 against 86)
-    if (grad || (!tg.pl_even && mv < 3)) {
+    if (tg.plain_mode != 0 && (grad || (!tg.pl_even && mv < 3))) {
       for (int c = 0; c < mv; ++c)
         if (!intrain[c]) plain_chain(tg, X, c, grad, psc, pv + c, pgr + c * d);
-    } else {
-      plain_tile(tg.dev, X.p, X.pitch, mv, intrain, pv);
+    } else if (tg.plain_mode != 0) {
+      // each wave takes its chains two at a time, which share the table's rows (stretch moves of 4096
+      // chains in BF16: 168 us a step one by one, 139 in pairs)
+      const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+      auto next = [&](int c) {
+        while (c < mv && __builtin_amdgcn_readfirstlane(intrain[c])) c += kWaves;
+        return c;
+      };
+      for (int c = next(wv); c < mv;) {
+        const int c2 = next(c + kWaves);
+        double v[2];
+        plain_wave<2>(tg, X, {c, c2 < mv ? c2 : c}, v);
+        if ((tid & 63) == 0) {
+          pv[c] = v[0];
+          if (c2 < mv) pv[c2] = v[1];
+        }
+        c = next(c2 + kWaves);
+      }
       __syncthreads();
     }
   }

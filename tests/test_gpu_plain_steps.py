@@ -85,3 +85,33 @@ def test_values_alone_with_the_plain_model_outside_the_training_box(prec, n):
     b = B.best_logL_grad(ctx, x)[0]
     assert np.array_equal(a[inside], b[inside])
     np.testing.assert_allclose(a[~inside], b[~inside], rtol=1e-11)
+
+
+@pytest.mark.parametrize("prec,cpb", [("bf16", 16), ("bf16", 32), ("bf16", 64), ("fp32", 16), ("fp64", 16)])
+def test_kernels_without_the_plain_model_equal_those_with_it(prec, cpb):
+    """plain_mode 0 has kernels of its own for values; with a training box as large as the prior box
+    plain_mode 1 does the same work in the others: evaluations (layer by layer and in tiles) and the moves that
+    need values alone, bit for bit."""
+    base = _problem(0, True)
+    base.update(train_lo=base["lower"], train_hi=base["upper"])
+    rng = np.random.default_rng(cpb)
+    w = base["upper"] - base["lower"]
+    x = (base["lower"] + rng.random((5000, base["d"])) * w).T.copy()
+    out = []
+    for mode in (0, 1):
+        p = dict(base, plain_mode=mode)
+        ctx = B.best_init(p, n_chains=160, precision=prec, seed=5, chains_per_block=cpb)
+        res = []
+        for n in (64, 5000):
+            for grad in (False, True):
+                lp, g = B.best_logL_grad(ctx, x[:, :n].copy(), want_grad=grad)
+                res += [lp] + ([g] if grad else [])
+        B.best_set_whitening(ctx, 0.5 * (base["lower"] + base["upper"]), np.diag(0.2 * w))
+        B.best_set_state(ctx, x[:, :160].copy())
+        for s, kw in (("mh", dict(mh_scale=0.5)), ("aies", {}), ("de", {})):
+            st = B.best_step(ctx, s, 3, **kw)
+            assert st["accepted"] > 0
+            res += [np.array(v) for v in B.best_get_state(ctx)[:2]]
+        out.append(res)
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
