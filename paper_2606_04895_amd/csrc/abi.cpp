@@ -251,22 +251,26 @@ static KArgs base_args(const best_ctx* h) {
 }
 
 // Largest batch evaluated layer by layer, every layer over the whole chip, instead of as tiles.  A
-// tile streams all weights through one CU, so a batch of few tiles costs a full round, 26 to 300 us,
-// whatever its size; the layers cost 2 nh kernels of 3 to 4 us until their work shows.  The lines are
-// where the two meet, network and type by network and type (log pi and gradient, us, tiles / layers;
-// values alone alike):
-//   BF16 256 x 4  64 points 22.6 / 28.5, never;  512 x 4  64 points 41.3 / 29.6, 1024 41.7 / 38.0,
-//   2048 41.9 / 48.9;  FP16 1024 x 5  64 points 187 / 57, 2048 168 / 114, 3072 168 / 148;
-//   1024 x 2  2048 points 51.9 / 40.2
-//   FP32 128 x 2  512 points 17.1 / 15.3;  256 x 4  2048 points 48.9 / 41.4;  512 x 4  64 points
-//   134 / 41, 2048 133 / 88, 3072 133 / 134;  1024 x 3  64 points 304 / 53, 2048 298 / 175
+// tile streams all weights through one CU, so a batch of few tiles costs a full round, 14 to 600 us,
+// whatever its size; the layers cost 2 nh kernels of 3 to 4 us until their work shows.  The limits are
+// cut-offs that no measured network loses by, short of where the two meet for most (log pi and gradient, us,
+// tiles / layers at the limit and at the next size measured; 64 points for the rest of the gain):
+//   BF16, 2 width points, width >= 512 (below, nh kernels cost more than a round: 256 x 2 64 points 16.0 /
+//   16.1, 256 x 4 22.4 / 25.7):  512 x 2  64: 21.8 / 16.0, 1024: 22.6 / 19.5, 1536: 22.7 / 23.9;  512 x 4  64:
+//   39.9 / 28.1, 1024: 40.5 / 36.5, 1536: 40.7 / 46.8;  1024 x 2  64: 55.9 / 20.8, 2048: 52.1 / 40.2, 3072: 53.2 /
+//   51.4;  1024 x 5  64: 186 / 56, 2048: 169 / 112, 3072: 169 / 148;  2048 x 3  64: 343 / 46, 4096: 306 / 304
+//   FP32, 2048 points, width >= 256 (128 x 2 64 points 16.6 / 17.3, 128 x 5 27.1 / 32.1):  256 x 2  64: 23.8 /
+//   16.3, 2048: 24.7 / 21.3, 3072: 24.8 / 27.8;  256 x 4  2048: 47.3 / 40.9, 3072: 48.2 / 45.7;  512 x 2  64: 51.0 /
+//   21.2, 2048: 52.3 / 49.5, 4096: 54.2 / 51.6;  512 x 4  64: 129 / 40, 2048: 129 / 89, 4096: 130 / 147;  1024 x 2
+//   2048: 162 / 153, 3072: 167 / 163;  1024 x 5  64: 591 / 96, 2048: 586 / 331, 4096: 594 / 575
+// These are tiles of 16 chains, a full round of the chip; a last round of wider tiles costs more.
 static int64_t layer_points(const best_ctx* h) {
   if (h->prec == BEST_FP64 || h->nh < 2 || h->tg.plain_mode == 2) return 0;
   if (layout_for(h->prec, 1, h->H, h->d, h->nh, 0, 2).total > kLdsMax) return 0;
   // activations and three panels, in the tiles' activation scratch
   const int64_t have = (int64_t)h->grid_cap * h->hsave_stride * vasize(h->prec);
   const int64_t per = (int64_t)h->H * (4 * h->nh + 3 * tsize(h->prec));
-  const int64_t most = h->prec == BEST_FP32 ? std::min(8 * h->H, 2048) : h->H >= 512 ? 2 * h->H : 0;
+  const int64_t most = h->prec == BEST_FP32 ? (h->H >= 256 ? 2048 : 0) : h->H >= 512 ? 2 * h->H : 0;
   return std::min<int64_t>(most, have / per / 16 * 16);
 }
 
@@ -1259,7 +1263,7 @@ int best_ess_noalloc(best_ctx* h, const float* record, int64_t T, double* ess_ou
   int cur = -1;
   HIPCHK(h, hipGetDevice(&cur));
   if (cur != h->dev) return fail(h, BEST_ESTATE, "best_ess_noalloc: the context's device is not current");
-  // carve mean [d N], ssq [d N] and the partial sums (at most 2^21 doubles, see ess_segments) out
+  // carve mean [d N], ssq [d N] and the partial sums (at most kEssPartials, see ess_segments) out
   // of the fixed array; the kernels write every element they later read, so nothing needs
   // clearing between calls
   double* mean = h->scratch;
