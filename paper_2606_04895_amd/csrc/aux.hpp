@@ -8,22 +8,28 @@ namespace best {
 
 constexpr int kEssLB = 32;   // lags per autocovariance window
 constexpr int kEssWin = 4;   // windows per launch after the first launch's single one
+// Partial sums of an autocovariance launch where a single time segment fits in that many.
+constexpr int64_t kEssPartials = (int64_t)1 << 21;
 // Time segments of the autocovariance launches: enough that 4096 waves (four per SIMD) share
 // the record, none shorter than 128 steps, and the partial sums of kEssWin windows no more than
-// 2^21 doubles where one segment fits in that (every size best_ess_noalloc takes).
+// kEssPartials doubles where one segment fits in that (every size best_ess_noalloc takes).
 inline int ess_segments(int64_t T, int d, int64_t N) {
   const int64_t rows = (int64_t)d * ((N + 63) / 64);
   int64_t n = (4096 + rows - 1) / rows;
   if (n > T / 128) n = T / 128;
-  const int64_t cap = ((int64_t)1 << 21) / (rows * kEssWin * kEssLB);
+  const int64_t cap = kEssPartials / (rows * kEssWin * kEssLB);
   if (n > cap) n = cap;
   return (int)(n < 1 ? 1 : n);
 }
 // Entry points that allocate nothing take their device scratch from one fixed array per
-// GPU (kernels_aux.hip).  The ESS passes need up to 4 d ceil(N/64) 64 doubles of it, so d times
-// the 64-padded chain count is limited to kNoAllocMaxDN (32 MiB of scratch per GPU).
+// GPU (kernels_aux.hip).  The ESS passes need the means and sums of squares, 2 d N doubles, and up
+// to kEssPartials partial sums, so d times the 64-padded chain count is limited to kNoAllocMaxDN (32 MiB
+// of scratch per GPU).
 constexpr int64_t kNoAllocMaxDN = (int64_t)1 << 20;
 constexpr int64_t kNoAllocScratchDoubles = 4 * kNoAllocMaxDN;
+static_assert(kNoAllocScratchDoubles >= 2 * kNoAllocMaxDN + kEssPartials &&
+                  kNoAllocMaxDN / 64 * kEssWin * kEssLB <= kEssPartials,
+              "fixed scratch: means, squares and one segment's partial sums of the largest record");
 
 // Templated per precision (kernels_<prec>.hip).
 hipError_t launch_step(int prec, int MT, const KArgs& a, int grid, size_t lds, hipStream_t s);
