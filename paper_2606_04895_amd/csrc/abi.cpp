@@ -10,6 +10,7 @@
 #include <string>
 #include <vector>
 
+#include "arena.hpp"
 #include "aux.hpp"
 #include "layout.hpp"
 
@@ -84,35 +85,24 @@ namespace {
 
 constexpr int kLdsMax = 163840;  // 160 KiB of LDS per CU on gfx950
 
-struct Arena {
-  std::vector<void*> ptrs;
+struct HipAlloc {
+  static bool alloc(void** p, size_t n) {
+    if (hipMalloc(p, n) == hipSuccess) return true;
+    (void)hipGetLastError();  // or the next launch would report it
+    return false;
+  }
+  static void free(void* p) { (void)hipFree(p); }
+};
+struct Arena : ArenaT<HipAlloc> {
   template <class T>
   hipError_t alloc(T** p, size_t n) {
-    *p = nullptr;
-    if (n == 0) n = 1;
-    void* q = nullptr;
-    hipError_t e = hipMalloc(&q, n * sizeof(T));
-    if (e != hipSuccess) return e;
-    ptrs.push_back(q);
-    *p = (T*)q;
-    return hipSuccess;
+    return ArenaT<HipAlloc>::alloc(p, n) ? hipSuccess : hipErrorOutOfMemory;
   }
   template <class T>
   hipError_t upload(T** p, const T* host, size_t n, hipStream_t s) {
     hipError_t e = alloc(p, n);
     if (e != hipSuccess) return e;
     return hipMemcpyAsync(*p, host, n * sizeof(T), hipMemcpyHostToDevice, s);
-  }
-  void release(void* p) {
-    auto it = std::find(ptrs.begin(), ptrs.end(), p);
-    if (it != ptrs.end()) {
-      (void)hipFree(*it);
-      ptrs.erase(it);
-    }
-  }
-  void free_all() {
-    for (void* p : ptrs) (void)hipFree(p);
-    ptrs.clear();
   }
 };
 
@@ -615,6 +605,8 @@ int best_init(best_ctx** out, const best_problem* p, const best_config* c) {
     return bail(BEST_EHIP);
   }
   h->dev = dev;
+  h->mem.spare = &h->met;
+  h->mem.spare_size = &h->met_cap;
   // the device's fixed scratch, resolved once per device with that device current
   h->scratch_err = noalloc_scratch_address(dev, &h->scratch);
   h->d = p->d;
@@ -1282,7 +1274,8 @@ namespace {
 // Device scratch of one metric call, carved from the context's metric buffer.  The buffer grows to
 // the largest call (growing frees the old one, which waits for the device) and is kept up to
 // kMetricKeep bytes: an allocation and release of a few hundred MB costs as much as the
-// kernels that use it (226 MB: 0.25 ms).  Larger ones are released at the end of the call.
+// kernels that use it (226 MB: 0.25 ms).  Larger ones are released at the end of the call, and any when
+// another allocation of the context fails.
 constexpr size_t kMetricKeep = (size_t)512 << 20;
 struct MetricScratch {
   best_ctx* h;
@@ -1291,7 +1284,6 @@ struct MetricScratch {
   ~MetricScratch() {
     if (h->met_cap > kMetricKeep) {
       h->mem.release(h->met);
-      h->met = nullptr;
       h->met_cap = 0;
     }
   }
@@ -1301,7 +1293,6 @@ struct MetricScratch {
     for (size_t b : parts) need += round(b);
     if (need <= h->met_cap) return true;
     h->mem.release(h->met);
-    h->met = nullptr;
     h->met_cap = 0;
     if (h->mem.alloc(&h->met, need) != hipSuccess) return false;
     h->met_cap = need;
