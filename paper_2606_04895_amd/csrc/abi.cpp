@@ -1569,7 +1569,6 @@ int best_sliced_wasserstein(best_ctx* h, const float* a, int64_t Ta, int64_t cha
 struct best_trainer {
   std::string err;
   hipStream_t stream = nullptr;
-  int n_cu = 256;
   int d = 0, H = 0, nh = 0, prec = BEST_FP32;
   int64_t np = 0, t = 0;
   Arena mem;
@@ -1654,9 +1653,9 @@ int best_trainer_create(best_trainer** out, int32_t d, int32_t width, int32_t n_
   t->nh = n_hidden;
   t->prec = precision;
   t->np = mlp_nparams_impl(d, width, n_hidden);
-  int dev = 0;
+  int dev = 0, n_cu = 0;  // the attribute's query fails where the device cannot be used
   hipError_t he = hipGetDevice(&dev);
-  if (he == hipSuccess) he = hipDeviceGetAttribute(&t->n_cu, hipDeviceAttributeMultiprocessorCount, dev);
+  if (he == hipSuccess) he = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
   if (he != hipSuccess)
     return bail(tfail(t, BEST_EHIP, std::string("no usable HIP device: ") + hipGetErrorString(he)));
   // whether the reverse pass takes the activations in the GEMM type: where tiles of 32 (16)

@@ -129,7 +129,7 @@ __host__ __device__ inline LdsLayout lds_layout(int M, int H, int d, int nh, int
   o = align16(o + waves * M * asize);
   L.out = o;
   o = align16(o + M * asize);
-  L.up = o;
+  L.up = o;  // [M] accumulators, in use by no kernel at present
   o = align16(o + M * asize);
   L.mi = o;  // ints: inbox[M], intrain[M], flag[M]
   o = align16(o + 4 * M * 4);
@@ -190,8 +190,8 @@ struct KArgs {
 };
 
 // ---------------------------------------------------------------------------------------
-// Plain spectrum log-likelihood of one chain, with its gradient if asked for, by the whole workgroup: an
-// exponential, a sine and a cosine per bin and term.
+// Plain spectrum log-likelihood of one chain and its gradient, by the whole workgroup: an exponential, a
+// sine and a cosine per bin and term.
 // ---------------------------------------------------------------------------------------
 // Element (i, c) of a tile's [d][M] FP64 array: the global SoA state (p = base + c0,
 // pitch = Np), a caller's array, or the tile's LDS scratch (pitch = M).
@@ -234,7 +234,7 @@ __device__ __forceinline__ double dot8(double acc, int j0, int j1, const FA& fa,
   return acc;
 }
 
-__device__ __forceinline__ void plain_chain(const Target& tg, const TView& X, int c, bool grad,
+__device__ __forceinline__ void plain_chain(const Target& tg, const TView& X, int c,
                                             double* scratch, double* outv, double* outg) {
   const int tid = local_tid(), d = tg.d, nt = tg.n_terms;
   double* tpl = scratch;                  // [kMaxD]
@@ -274,31 +274,27 @@ __device__ __forceinline__ void plain_chain(const Target& tg, const TView& X, in
     const double dr = spec - tg.data[j];
     const double r = dr * tg.w2[j];
     ll += dr * r;
-    if (grad) {
 #pragma unroll
-      for (int m = 0; m < kMaxTerms; ++m) {
-        if (m < nt) {
-          const double ec = e[m] * co[m];
-          sec[m] += r * ec;
-          sxec[m] += r * xj * ec;
-          ses[m] += r * (e[m] * si[m]);
-        }
+    for (int m = 0; m < kMaxTerms; ++m) {
+      if (m < nt) {
+        const double ec = e[m] * co[m];
+        sec[m] += r * ec;
+        sxec[m] += r * xj * ec;
+        ses[m] += r * (e[m] * si[m]);
       }
     }
   }
   const int lane = tid & 63, wv = tid >> 6;
   ll = wave_sum(ll);
   if (lane == 0) wred[wv * 32] = ll;
-  if (grad) {
 #pragma unroll
-    for (int m = 0; m < kMaxTerms; ++m) {
-      if (m < nt) {
-        const double a = wave_sum(sec[m]), b = wave_sum(sxec[m]), c = wave_sum(ses[m]);
-        if (lane == 0) {
-          wred[wv * 32 + 1 + m] = a;
-          wred[wv * 32 + 1 + kMaxTerms + m] = b;
-          wred[wv * 32 + 1 + 2 * kMaxTerms + m] = c;
-        }
+  for (int m = 0; m < kMaxTerms; ++m) {
+    if (m < nt) {
+      const double a = wave_sum(sec[m]), b = wave_sum(sxec[m]), c = wave_sum(ses[m]);
+      if (lane == 0) {
+        wred[wv * 32 + 1 + m] = a;
+        wred[wv * 32 + 1 + kMaxTerms + m] = b;
+        wred[wv * 32 + 1 + 2 * kMaxTerms + m] = c;
       }
     }
   }
@@ -308,7 +304,7 @@ __device__ __forceinline__ void plain_chain(const Target& tg, const TView& X, in
     for (int w = 1; w < kWaves; ++w) s += wred[w * 32];
     *outv = -0.5 * s;
   }
-  if (grad && tid < d) {
+  if (tid < d) {
     double dt = 0;
     for (int m = 0; m < nt; ++m) {
       double s1 = 0, s2 = 0, s3 = 0;
@@ -1329,7 +1325,7 @@ __device__ __forceinline__ void eval_tile(const KArgs& a, char* smem, typename P
     // point 40 us against 74 by a wave, four 156 against 86)
     if (tg.plain_mode != 0 && (grad || (!tg.pl_even && mv < 3))) {
       for (int c = 0; c < mv; ++c)
-        if (!intrain[c]) plain_chain(tg, X, c, grad, psc, pv + c, pgr + c * d);
+        if (!intrain[c]) plain_chain(tg, X, c, psc, pv + c, pgr + c * d);
     } else if (tg.plain_mode != 0) {
       // each wave takes its chains two at a time, which share the table's rows (stretch moves of 4096
       // chains in BF16: 168 us a step one by one, 139 in pairs)

@@ -390,7 +390,7 @@ __device__ __forceinline__ void load_rows(const V* __restrict__ base, int rt, in
 //   sync_in:    the caller wrote s.thf without a barrier; the input layer joins one after
 //               issuing its weight loads;
 //   defer_out:  leave the per-wave output partials in s.outp and return without a barrier;
-//               mlp_backward(..., finish_out) completes s.out.
+//               mlp_backward (its closing part, mlp_input_grad) completes s.out.
 template <class P, int MT>
 __device__ __forceinline__ void mlp_forward(const MlpParams& mp, const MlpSmem<P>& s,
                                             typename P::acc* __restrict__ hsave, bool fuse_delta,
