@@ -133,9 +133,11 @@ __device__ __forceinline__ void gemm_pass_rg(int n_layers, int KS, int rtw0, int
   using acc = typename P::acc;
   constexpr int D = prefetch_depth<MT>();
   // FP32 MFMAs leave 32 cycles for every LDS read and ring load if these are issued step by step, and
-  // the compiler would gather them at the end of the unrolled steps (512 x 4, burn-in of MALA on 4096
-  // chains: 5.81 -> 5.78 ms pinned; 16-bit NUTS on 1024 x 5: 13.1 -> 13.3 ms, left free)
-  constexpr bool kPinned = sizeof(T) == 4;
+  // the compiler would gather them at the end of the unrolled steps.  That pays on tiles of 16 chains alone
+  // (ms, free / pinned; HMC on 6 -> 512 x 4: 4096 chains 4.84 / 4.81; MALA on 12 -> 1024 x 4, 4096 chains,
+  // 4.45 / 4.47); wider tiles have enough MFMAs to a step (8192 chains 4.29 / 4.38, 16384 chains 8.46 / 8.62,
+  // 65536 points 1.69 / 1.73; 16-bit NUTS on 1024 x 5 13.1 / 13.3)
+  constexpr bool kPinned = sizeof(T) == 4 && MT == 1;
   const int lane = local_tid() & 63;
   const int ng = RTW / RG;
   frag a[D][RG];
