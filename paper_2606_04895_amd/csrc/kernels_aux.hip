@@ -385,13 +385,16 @@ __global__ __launch_bounds__(kAuxThreads) void moments_final_kernel(
 // passes wherever the chain starts.  (As S2 - S1^2 / T about the chain's first value it grows T times for
 // a chain that starts far from its mean.)  Means are taken relative to that first value, from which
 // neighbouring floats differ exactly.  Bound by the record's bytes: 4000 x 6 x 4096 (393 MB) 93 us; a
-// thread per chain with two passes took 3190 us.
+// thread per chain with two passes took 3190 us.  A record of few chains has few workgroups and is bound by
+// their FP64 instructions: so the mask stands in the last block alone, the reciprocals of 64 blocks
+// are taken by the 64 lanes at once, and two workgroups share a CU (at most 64 VGPRs).  The ESS of 42 x 6
+// chains x 3820 steps takes 129 us (142 with a mask and a division in every block), of 900 x 20 x 300 73 us (79).
 constexpr int kStatWaves = 16, kStatBlock = 8;
 struct StatSteps {  // the first waves have n_hi steps each, the others one less; reciprocals (0 of 0)
   int64_t n_hi;
   double r_T, r_hi, r_lo, tail_hi, tail_lo;  // tail: of the steps in the last block
 };
-__global__ __launch_bounds__(64 * kStatWaves) void ess_chain_stats_kernel(const float* rec,
+__global__ __launch_bounds__(64 * kStatWaves, 8) void ess_chain_stats_kernel(const float* rec,
                                                                           int64_t T, int d,
                                                                           int64_t N, StatSteps n,
                                                                           double* mean,
@@ -407,22 +410,39 @@ __global__ __launch_bounds__(64 * kStatWaves) void ess_chain_stats_kernel(const 
     const float* __restrict__ x = rec + (int64_t)i * N + cb * 64;  // scalar; lane offset cl
     const double x0 = x[cl];
     double s1 = 0, q = 0, rk = 0;  // over the wave's first k values: sum, squares about their mean, 1 / k
-    float next[kStatBlock];
-    auto load = [&](int64_t k) {
-      const float* p = x + (wv + k * kStatWaves) * st;
-#pragma unroll
-      for (int u = 0; u < kStatBlock; ++u) {
-        next[u] = p[cl];
-        if (k + u + 1 < n_w) p += kStatWaves * st;
-      }
-    };
-    if (n_w > 0) load(0);
-    for (int64_t k = 0; k < n_w; k += kStatBlock) {
-      const int nb = n_w - k < kStatBlock ? (int)(n_w - k) : kStatBlock;
+    const float* p = x + wv * st;
+    double rtab = 0;  // lane l: one over the values up to block l of 64
+    int64_t k = 0;
+    for (; k + kStatBlock <= n_w; k += kStatBlock) {
+      const int kb = (int)(k / kStatBlock) & 63;
+      if (kb == 0) rtab = 1.0 / (double)(k + (lane + 1) * kStatBlock);
       float v[kStatBlock];
 #pragma unroll
-      for (int u = 0; u < kStatBlock; ++u) v[u] = next[u];
-      if (k + kStatBlock < n_w) load(k + kStatBlock);
+      for (int u = 0; u < kStatBlock; ++u) {
+        v[u] = p[cl];
+        p += kStatWaves * st;
+      }
+      const double c0 = v[0];
+      double sb = 0, qb = 0;
+#pragma unroll
+      for (int u = 1; u < kStatBlock; ++u) {
+        const double y = (double)v[u] - c0;
+        sb += y;
+        qb += y * y;
+      }
+      const double off = c0 - x0, dm = k ? (off + sb * (1.0 / kStatBlock)) - s1 * rk : 0.0;
+      rk = lane_value(rtab, kb);
+      q += (qb - sb * (sb * (1.0 / kStatBlock))) + dm * dm * ((double)k * (double)kStatBlock * rk);
+      s1 += off * (double)kStatBlock + sb;
+    }
+    if (k < n_w) {
+      const int nb = (int)(n_w - k);
+      float v[kStatBlock];  // the last value again past the end
+#pragma unroll
+      for (int u = 0; u < kStatBlock; ++u) {
+        v[u] = p[cl];
+        if (k + u + 1 < n_w) p += kStatWaves * st;
+      }
       const double c0 = v[0];
       double sb = 0, qb = 0;
 #pragma unroll
@@ -431,10 +451,9 @@ __global__ __launch_bounds__(64 * kStatWaves) void ess_chain_stats_kernel(const 
         sb += y;
         qb += y * y;
       }
-      const double rb = k + kStatBlock <= n_w ? 1.0 / kStatBlock : n_w == n.n_hi ? n.tail_hi : n.tail_lo;
-      const double off = c0 - x0, dm = k ? (off + sb * rb) - s1 * rk : 0.0;
-      rk = k + nb < n_w ? 1.0 / (double)(k + nb) : n_w == n.n_hi ? n.r_hi : n.r_lo;
-      q += (qb - sb * (sb * rb)) + dm * dm * ((double)k * (double)nb * rk);
+      const double rb = n_w == n.n_hi ? n.tail_hi : n.tail_lo, off = c0 - x0;
+      const double dm = k ? (off + sb * rb) - s1 * rk : 0.0;
+      q += (qb - sb * (sb * rb)) + dm * dm * ((double)k * (double)nb * (n_w == n.n_hi ? n.r_hi : n.r_lo));
       s1 += off * (double)nb + sb;
     }
     sh[0][wv][lane] = s1;
