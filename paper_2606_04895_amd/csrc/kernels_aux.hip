@@ -388,11 +388,11 @@ __global__ __launch_bounds__(kAuxThreads) void moments_final_kernel(
 // thread per chain with two passes took 3190 us.  A record of few chains has few workgroups and is bound by
 // their FP64 instructions: so the mask stands in the last block alone, the reciprocals of 64 blocks
 // are taken by the 64 lanes at once, and two workgroups share a CU (at most 64 VGPRs).  The ESS of 42 x 6
-// chains x 3820 steps takes 129 us (142 with a mask and a division in every block), of 900 x 20 x 300 73 us (79).
+// chains x 3820 steps takes 127 us (142 with a mask and a division in every block), of 900 x 20 x 300 72 us (79).
 constexpr int kStatWaves = 16, kStatBlock = 8;
-struct StatSteps {  // the first waves have n_hi steps each, the others one less; reciprocals (0 of 0)
-  int64_t n_hi;
-  double r_T, r_hi, r_lo, tail_hi, tail_lo;  // tail: of the steps in the last block
+struct StatSteps {  // the first n_split waves have d_hi steps each, the others d_lo, one less
+  int n_split;
+  double d_hi, d_lo, r_T, r_hi, r_lo, tail_hi, tail_lo;  // r: reciprocals (0 of 0), tail: of the last block's steps
 };
 __global__ __launch_bounds__(64 * kStatWaves, 8) void ess_chain_stats_kernel(const float* rec,
                                                                           int64_t T, int d,
@@ -413,6 +413,7 @@ __global__ __launch_bounds__(64 * kStatWaves, 8) void ess_chain_stats_kernel(con
     const float* p = x + wv * st;
     double rtab = 0;  // lane l: one over the values up to block l of 64
     int64_t k = 0;
+    double kd = 0;  // k
     for (; k + kStatBlock <= n_w; k += kStatBlock) {
       const int kb = (int)(k / kStatBlock) & 63;
       if (kb == 0) rtab = 1.0 / (double)(k + (lane + 1) * kStatBlock);
@@ -430,9 +431,10 @@ __global__ __launch_bounds__(64 * kStatWaves, 8) void ess_chain_stats_kernel(con
         sb += y;
         qb += y * y;
       }
-      const double off = c0 - x0, dm = k ? (off + sb * (1.0 / kStatBlock)) - s1 * rk : 0.0;
+      const double off = c0 - x0, dm = (off + sb * (1.0 / kStatBlock)) - s1 * rk;
       rk = lane_value(rtab, kb);
-      q += (qb - sb * (sb * (1.0 / kStatBlock))) + dm * dm * ((double)k * (double)kStatBlock * rk);
+      q += (qb - sb * (sb * (1.0 / kStatBlock))) + dm * dm * (kd * (double)kStatBlock * rk);
+      kd += (double)kStatBlock;
       s1 += off * (double)kStatBlock + sb;
     }
     if (k < n_w) {
@@ -447,13 +449,14 @@ __global__ __launch_bounds__(64 * kStatWaves, 8) void ess_chain_stats_kernel(con
       double sb = 0, qb = 0;
 #pragma unroll
       for (int u = 1; u < kStatBlock; ++u) {
-        const double y = u < nb ? (double)v[u] - c0 : 0.0;
+        if (u >= nb) break;  // the same in every lane
+        const double y = (double)v[u] - c0;
         sb += y;
         qb += y * y;
       }
-      const double rb = n_w == n.n_hi ? n.tail_hi : n.tail_lo, off = c0 - x0;
-      const double dm = k ? (off + sb * rb) - s1 * rk : 0.0;
-      q += (qb - sb * (sb * rb)) + dm * dm * ((double)k * (double)nb * (n_w == n.n_hi ? n.r_hi : n.r_lo));
+      const double rb = wv < n.n_split ? n.tail_hi : n.tail_lo, off = c0 - x0;
+      const double dm = (off + sb * rb) - s1 * rk;
+      q += (qb - sb * (sb * rb)) + dm * dm * (kd * (double)nb * (wv < n.n_split ? n.r_hi : n.r_lo));
       s1 += off * (double)nb + sb;
     }
     sh[0][wv][lane] = s1;
@@ -461,14 +464,13 @@ __global__ __launch_bounds__(64 * kStatWaves, 8) void ess_chain_stats_kernel(con
     __syncthreads();
     if (wv == 0 && c < N) {
       s1 = q = 0;
-#pragma unroll 4
+#pragma unroll 8
       for (int w = 0; w < kStatWaves; ++w) s1 += sh[0][w][lane];  // zero for a wave without steps
       const double m = s1 * n.r_T;
-#pragma unroll 4
+#pragma unroll 8
       for (int w = 0; w < kStatWaves; ++w) {
-        const int64_t nw = (T - w + kStatWaves - 1) / kStatWaves;
-        const double dm = sh[0][w][lane] * (nw == n.n_hi ? n.r_hi : n.r_lo) - m;
-        q += sh[1][w][lane] + (double)nw * (dm * dm);
+        const double dm = sh[0][w][lane] * (w < n.n_split ? n.r_hi : n.r_lo) - m;
+        q += sh[1][w][lane] + (w < n.n_split ? n.d_hi : n.d_lo) * (dm * dm);
       }
       mean[i * N + c] = x0 + m;
       ssq[i * N + c] = q;
@@ -1045,7 +1047,8 @@ hipError_t launch_ess_chain_stats(const float* rec, int64_t T, int d, int64_t N,
                                   double* ssq, hipStream_t s) {
   const int64_t hi = (T + kStatWaves - 1) / kStatWaves, lo = hi - 1;
   auto inv = [](int64_t n) { return n ? 1.0 / (double)n : 0.0; };
-  const StatSteps n{hi, 1.0 / (double)T, inv(hi), inv(lo), inv(hi % kStatBlock), inv(lo % kStatBlock)};
+  const StatSteps n{(int)(T - lo * kStatWaves), (double)hi, (double)lo, 1.0 / (double)T, inv(hi), inv(lo),
+                    inv(hi % kStatBlock), inv(lo % kStatBlock)};
   hipLaunchKernelGGL(ess_chain_stats_kernel,
                      dim3((unsigned)capped_blocks((N + 63) / 64, 64 * kStatWaves), (unsigned)d),
                      dim3(64 * kStatWaves), 0, s, rec, T, d, N, n, mean, ssq);
