@@ -263,7 +263,9 @@ __device__ __forceinline__ void gemm_in(const typename IP::T* __restrict__ A, in
 }
 
 // Input layer over this wave's RTW row tiles: eight at once when the input fits one k-step, else four
-// or two where they divide the tiles, else one by one.
+// where they divide the tiles, else two, else one by one.  The first of these stands outside the loop: a wave
+// that has only one pays for the loop otherwise (HMC on 55 chains of 6 -> 128 x 2 in FP16, 4.59 ms against
+// 4.70 with it inside).
 template <class IP, int MT, class Pre, class Epi>
 __device__ __forceinline__ void gemm_in_rows(const typename IP::T* A, int KS,
                                              const typename IP::T* Bl, int rtw0, int RTW,
@@ -277,8 +279,8 @@ __device__ __forceinline__ void gemm_in_rows(const typename IP::T* A, int KS,
   } else if (RTW == 2) {
     gemm_in<IP, 2, MT, kMaxKs1>(A, KS, Bl, rtw0, pre, epi, sync);
   } else {
-    for (int r = 0; r < RTW; ++r)
-      gemm_in<IP, 1, MT, kMaxKs1>(A, KS, Bl, rtw0 + r, pre, epi, sync && r == 0);
+    gemm_in<IP, 1, MT, kMaxKs1>(A, KS, Bl, rtw0, pre, epi, sync);
+    for (int r = 1; r < RTW; ++r) gemm_in<IP, 1, MT, kMaxKs1>(A, KS, Bl, rtw0 + r, pre, epi, false);
   }
 }
 
