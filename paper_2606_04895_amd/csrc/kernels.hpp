@@ -1658,7 +1658,7 @@ __device__ __forceinline__ void commit_tile(const State& S, const Scratch& T, co
 // ---------------------------------------------------------------------------------------
 // Metropolis-Hastings on lane groups (the expressions of the loop form in mh_tile, in their
 // order).  A step of a small tile is a serial chain of FP64 latencies, not work: 16 chains of 6
-// parameters on 6 -> 128 x 2 in FP64 took 19.1 us a step as loops and take 14.5 here, of which the
+// parameters on 6 -> 128 x 2 in FP64 took 19.1 us a step as loops and take 14.1 here, of which the
 // matrix instructions need 1.8.  So no step waits for memory or for a barrier that the emulator does not need: the chains' points
 // and log pi stay in the tile's scratch (written through to the state when a move is accepted),
 // step s's normals and log u are drawn during step s - 1 by the waves that hold no chain, and the

@@ -447,8 +447,8 @@ __global__ __launch_bounds__(256) void fit_layer_kernel(FitArgs a, int l) {
 // Closing kernel of a layer-by-layer evaluation: one column tile per workgroup takes the network's
 // output from h_{nh-1}, d out / d t from delta_0 and assembles log pi and its gradient, in the
 // tile engine's order throughout.  Bound by latency, like the layers of a small batch (64 points of
-// 12 -> 512 x 4: 7 us here, 3.5 us a layer; one tile per CU through all weights took 41 us, the eight
-// kernels take 30).
+// 12 -> 512 x 4: 6.3 us here, 3.5 us a layer; one tile per CU through all weights took 41 us, the eight
+// kernels take 28).
 template <class P>
 __global__ __launch_bounds__(kThreads) void eval_close_kernel(KArgs a, FitArgs f) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
